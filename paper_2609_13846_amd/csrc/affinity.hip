@@ -29,7 +29,7 @@
 // matching concatenation [x | a_0 | ... | a_{H-1}] of the caller's x and attn, tiled once
 // per slice so that every fragment load is contiguous; the fused kernel is one
 // contraction over d + H*dh with epilogues at the operating-point and head boundaries.
-// The fp32 path (dtype DTP_F32) runs the same decomposition with plain FMA kernels.
+// The fp32 path (dtype DTP_F32, affinity_f32.hip) runs the same decomposition on fp32 MFMAs.
 #include <atomic>
 #include <cmath>
 #include <vector>
@@ -50,7 +50,6 @@ constexpr int kSliceTokens = 1 << 18;  // tokens per internal slice (size of the
 constexpr int kMaxSplits = 128;        // token splits per launch (size of the partials)
 constexpr int kTileTokens = 1 << 15;   // tokens per bf16 slice (size of the tiled token buffer)
 constexpr int kTargetBlocks = 768;     // bf16 kernel: aim for this many blocks per launch
-constexpr int kTargetBlocksF32 = 768;  // fp32 kernel: the same, in blocks of 4 waves
 constexpr size_t kLdsPerCu = 160 * 1024;  // LDS bytes per CU (gfx950)
 
 template <typename T>
@@ -172,24 +171,6 @@ fold_kernel(uint16_t* __restrict__ wcat, const uint16_t* __restrict__ woT, int N
       const int m = m0 + wave * 32 + acc_row(i, lane);
       wcat[(int64_t)m * ld + d + n] = f32_to_bf16(acc[b][i]);
     }
-  }
-}
-
-// fp32 fold: F[h][gu][k][e] = sum_j W_o[j][h*dh + e] * gamma[j] * W_gu[k][j]
-__global__ void fold_f32_kernel(const float* __restrict__ w_o, const float* __restrict__ gamma,
-                                const float* __restrict__ w_gate, const float* __restrict__ w_up,
-                                int d, int I, int H, int dh, float* __restrict__ fold) {
-  const int64_t total = (int64_t)H * 2 * I * dh;
-  for (int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; idx < total;
-       idx += (int64_t)gridDim.x * blockDim.x) {
-    const int e = (int)(idx % dh);
-    const int k = (int)((idx / dh) % I);
-    const int gu = (int)((idx / ((int64_t)dh * I)) % 2);
-    const int h = (int)(idx / ((int64_t)dh * I * 2));
-    const float* w = (gu == 0 ? w_gate : w_up) + (int64_t)k * d;
-    float s = 0.0f;
-    for (int j = 0; j < d; ++j) s = fmaf(w_o[(int64_t)j * H * dh + h * dh + e] * gamma[j], w[j], s);
-    fold[idx] = s;
   }
 }
 
@@ -1002,6 +983,8 @@ bool affinity_lds_fits(size_t dynamic, size_t margin = 0) {
   return static_lds + dynamic + margin <= kLdsPerCu;
 }
 
+}  // namespace
+
 // Compute units of the current device, cached per device (atomics: calls on different
 // layers may run on several host threads at once).
 int device_cus() {
@@ -1042,6 +1025,8 @@ int choose_splits(int groups, int mtiles) {
   return best;
 }
 
+namespace {
+
 // Launches the fused kernel on one slice; returns the number of token splits used, or 0
 // if a block does not fit the LDS.
 template <int KC, int WM, int WN, int RB, int NB, bool PACK, int SG, bool ADD, int RING>
@@ -1073,81 +1058,6 @@ int launch_affinity_copied(AffinityArgs p, hipStream_t s) {
   if (affinity_lds_fits<KC, 8, 1, 1, 2, true, 4, ADD, 6>(affinity_dynamic_lds<8, 1, 2>(p.G), 8192))
     return launch_affinity<KC, 8, 1, 1, 2, true, 4, ADD, 6>(p, s);
   return launch_affinity<KC, 8, 1, 1, 2, true, 4, ADD, 3>(p, s);
-}
-
-// ------------------------------------------------------------------ fused affinity (fp32)
-// One thread per (neuron, token lane); heads visited group by group.
-struct AffinityF32Args {
-  const float* x;      // [T][d]
-  const float* attn;   // [T][H*dh]
-  const float* wgu;    // [n_tiles*128][d] gamma-scaled gate | up rows per tile
-  const float* fold;   // [H][2][I][dh]
-  const float* rinv;
-  const float* rinv_next;  // or NULL
-  const float* nd;
-  float* partial;      // [splits][G+1][I_pad]
-  int T, d, H, G, dh, I, I_pad, splits;
-  int add;             // ADD score instead of FO
-};
-
-__global__ void __launch_bounds__(256)
-affinity_f32_kernel(AffinityF32Args p) {
-  // blockDim = 256 = 4 token lanes x 64 neurons of one tile
-  __shared__ float red[4][kMaxAffinityGroups + 1][kBN];
-  const int kl = threadIdx.x & 63, tl = threadIdx.x >> 6;
-  const int tile = blockIdx.x / p.splits, split = blockIdx.x % p.splits;
-  const int k = tile * kBN + kl;
-  const int HD = p.H * p.dh, hpg = p.H / p.G;
-  const int per = (p.T + p.splits - 1) / p.splits;
-  const int t0 = split * per, t1 = min(p.T, t0 + per);
-  float acc[kMaxAffinityGroups + 1];
-  for (int g = 0; g <= p.G; ++g) acc[g] = 0.0f;
-  if (k < p.I) {
-    const float* wg = p.wgu + (int64_t)tile * kCols * p.d + (int64_t)kl * p.d;
-    const float* wu = wg + (int64_t)kBN * p.d;
-    for (int t = t0 + tl; t < t1; t += 4) {
-      const float* xr = p.x + (int64_t)t * p.d;
-      const float ri = p.rinv[t];
-      float g = 0.0f, u = 0.0f;
-      for (int j = 0; j < p.d; ++j) {
-        g = fmaf(wg[j], xr[j], g);
-        u = fmaf(wu[j], xr[j], u);
-      }
-      g *= ri;
-      u *= ri;
-      const float sg = 1.0f / (1.0f + expf(-g));
-      if (p.rinv_next) {
-        const float a = g * sg * u * p.rinv_next[t];
-        acc[p.G] = fmaf(a, a, acc[p.G]);
-      }
-      const float cc2 = p.add ? ri : g * sg * ri;
-      const float cc1 = p.add ? ri : sg * (1.0f + g * (1.0f - sg)) * u * ri;
-      for (int h = 0; h < p.H; ++h) {
-        const float* ar = p.attn + (int64_t)t * HD + h * p.dh;
-        const float* fg = p.fold + (((int64_t)h * 2 + 0) * p.I + k) * p.dh;
-        const float* fu = p.fold + (((int64_t)h * 2 + 1) * p.I + k) * p.dh;
-        float pg = 0.0f, pu = 0.0f;
-        for (int e = 0; e < p.dh; ++e) {
-          pg = fmaf(ar[e], fg[e], pg);
-          pu = fmaf(ar[e], fu[e], pu);
-        }
-        if (p.add) {
-          acc[h / hpg] = fmaf(cc1 * pg, cc1 * pg, fmaf(cc2 * pu, cc2 * pu, acc[h / hpg]));
-        } else {
-          const float dl = cc1 * pg + cc2 * pu;
-          acc[h / hpg] = fmaf(dl, dl, acc[h / hpg]);
-        }
-      }
-    }
-  }
-  for (int g = 0; g <= p.G; ++g) red[tl][g][kl] = acc[g];
-  __syncthreads();
-  for (int i = threadIdx.x; i < (p.G + 1) * kBN; i += 256) {
-    const int g = i / kBN, kk = i % kBN;
-    const float s = red[0][g][kk] + red[1][g][kk] + red[2][g][kk] + red[3][g][kk];
-    const int n = tile * kBN + kk;
-    p.partial[((int64_t)split * (p.G + 1) + g) * p.I_pad + n] = g < p.G && !p.add ? s * p.nd[n] : s;
-  }
 }
 
 // A[g][k] += sum_s partial[s][g][k] for g < G (row g = blockIdx.y), and s_down[k] +=
@@ -1192,9 +1102,8 @@ struct dtp_layer_s {
   int device = 0;
   int n_tiles = 0, I_pad = 0, Kt = 0;
   bool has_weights = false;
-  void* w = nullptr;       // bf16 wcat [n_tiles*128][d + H*dh]; f32 W' [n_tiles*128][d]
+  void* w = nullptr;       // wcat [n_tiles*128][d + H*dh] in the layer's dtype
   void* woT = nullptr;     // bf16 [H*dh][d]: W_o^T, operand of the fold
-  float* fold32 = nullptr;   // f32 path: [H][2][I][dh]
   float* nd = nullptr;       // [I_pad]
   float* rinv = nullptr;     // [kSliceTokens]
   float* rinv_next = nullptr;  // [kSliceTokens], 1/r' for the down statistic
@@ -1208,7 +1117,7 @@ struct dtp_layer_s {
 namespace {
 
 void layer_free(dtp_layer L) {
-  void* bufs[] = {L->w, L->woT, L->fold32, L->nd, L->rinv, L->rinv_next, L->partial, L->xt};
+  void* bufs[] = {L->w, L->woT, L->nd, L->rinv, L->rinv_next, L->partial, L->xt};
   for (void* b : bufs)
     if (b) (void)hipFree(b);
   for (auto& e : L->events) {
@@ -1300,10 +1209,8 @@ dtp_status accumulate(dtp_layer L, const void* x, const void* attn, const void* 
       rms_kernel<uint16_t><<<rb, 256, 0, s>>>((const uint16_t*)xs, T, dm, d.rms_eps, L->rinv);
       if (xns)
         rms_kernel<uint16_t><<<rb, 256, 0, s>>>((const uint16_t*)xns, T, dm, eps_next, L->rinv_next);
-    } else {
-      rms_kernel<float><<<rb, 256, 0, s>>>((const float*)xs, T, dm, d.rms_eps, L->rinv);
-      if (xns)
-        rms_kernel<float><<<rb, 256, 0, s>>>((const float*)xns, T, dm, eps_next, L->rinv_next);
+    } else if (xns) {  // the fp32 kernel takes 1/r from the rows that it stages
+      rms_kernel<float><<<rb, 256, 0, s>>>((const float*)xns, T, dm, eps_next, L->rinv_next);
     }
     DTP_HIP(hipGetLastError());
     const float* rinv_next = xns ? L->rinv_next : nullptr;
@@ -1363,27 +1270,24 @@ dtp_status accumulate(dtp_layer L, const void* x, const void* attn, const void* 
       DTP_CHECK(splits > 0, DTP_ERR_UNSUPPORTED,
                 "affinity kernel: %d groups need more LDS than a CU holds", G);
     } else {
-      splits = (kTargetBlocksF32 + L->n_tiles - 1) / L->n_tiles;
-      splits = std::max(1, std::min(splits, std::min(T, kMaxSplits)));
       AffinityF32Args p;
       p.x = (const float*)xs;
       p.attn = (const float*)as;
-      p.wgu = (const float*)L->w;
-      p.fold = L->fold32;
-      p.rinv = L->rinv;
+      p.wcat = (const float*)L->w;
       p.rinv_next = rinv_next;
       p.nd = L->nd;
       p.partial = L->partial;
+      p.eps = d.rms_eps;
       p.T = T;
       p.d = dm;
       p.H = H;
       p.G = G;
       p.dh = dh;
-      p.I = I;
+      p.Kt = L->Kt;
       p.I_pad = L->I_pad;
-      p.splits = splits;
+      p.splits = 0;
       p.add = add ? 1 : 0;
-      affinity_f32_kernel<<<L->n_tiles * splits, 256, 0, s>>>(p);
+      splits = launch_affinity_f32(p, device_cus(), s);
     }
     DTP_HIP(hipGetLastError());
     if (L->profiling) {
@@ -1434,17 +1338,15 @@ dtp_status dtp_layer_create(const dtp_layer_desc* desc, dtp_layer* out) {
     L->I_pad = L->n_tiles * kBN;
     const int64_t HD = (int64_t)d.n_q_heads * d.head_dim;
     const size_t rows = (size_t)L->n_tiles * kCols;
+    L->Kt = d.d_model + (int)HD;
     if (d.dtype == DTP_BF16) {
-      L->Kt = d.d_model + (int)HD;
       // Element offsets inside the tiled slice stay below 2^30.
       L->tile_slice = std::max<int64_t>(256, std::min<int64_t>(kTileTokens, ((int64_t)1 << 30) / L->Kt) / 256 * 256);
       if (e == hipSuccess) e = hipMalloc(&L->w, 2 * rows * L->Kt);
       if (e == hipSuccess) e = hipMalloc(&L->woT, 2 * (size_t)HD * d.d_model);
       if (e == hipSuccess) e = hipMalloc(&L->xt, 2 * (size_t)L->tile_slice * L->Kt);
     } else {
-      L->Kt = d.d_model;
-      if (e == hipSuccess) e = hipMalloc(&L->w, 4 * rows * d.d_model);
-      if (e == hipSuccess) e = hipMalloc(&L->fold32, 4 * (size_t)HD * 2 * d.n_neurons);
+      if (e == hipSuccess) e = hipMalloc(&L->w, 4 * rows * L->Kt);
     }
     if (e == hipSuccess) e = hipMalloc(&L->nd, 4 * (size_t)L->I_pad);
     if (e == hipSuccess) e = hipMalloc(&L->rinv, 4 * (size_t)kSliceTokens);
@@ -1512,13 +1414,10 @@ dtp_status dtp_layer_set_weights(dtp_layer L, const void* w_o, const void* gamma
       if (st != DTP_OK) return st;
     } else {
       prep_gate_up_kernel<float><<<grid_for(n, 256), 256, 0, s>>>(
-          (const float*)w_gate, (const float*)w_up, (const float*)gamma, I, dm, L->n_tiles, dm,
+          (const float*)w_gate, (const float*)w_up, (const float*)gamma, I, dm, L->n_tiles, L->Kt,
           (float*)L->w);
       DTP_HIP(hipGetLastError());
-      const int64_t nf = (int64_t)H * 2 * I * dh;
-      fold_f32_kernel<<<grid_for(nf, 256), 256, 0, s>>>((const float*)w_o, (const float*)gamma,
-                                                         (const float*)w_gate, (const float*)w_up,
-                                                         dm, I, H, dh, L->fold32);
+      launch_fold_f32((float*)L->w, (const float*)w_o, L->n_tiles * kCols, HD, dm, L->Kt, s);
       DTP_HIP(hipGetLastError());
       st = down_norms((const float*)w_down, L, s);
       if (st != DTP_OK) return st;

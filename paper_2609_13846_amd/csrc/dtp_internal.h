@@ -65,6 +65,28 @@ constexpr int kMantBits = 40;
 hipError_t stream_alloc(void** p, size_t bytes, hipStream_t s);
 hipError_t stream_free(void* p, hipStream_t s);
 
+// ---- launch shapes of the affinity kernels (affinity.hip): the current device's compute
+// units, and the token splits of a launch of `groups` neuron groups x `mtiles` token tiles.
+int device_cus();
+int choose_splits(int groups, int mtiles);
+
+// ---- fp32 affinity path (affinity_f32.hip)
+struct AffinityF32Args {
+  const float* x;          // [T][d]
+  const float* attn;       // [T][H*dh]
+  const float* wcat;       // [2 I_pad][Kt] folded rows, Kt = d + H*dh: 64 gate, 64 up per tile
+  const float* rinv_next;  // [T] 1/r' of the residual entering the next layer, or NULL
+  const float* nd;         // [I_pad]
+  float* partial;          // [splits][G+1][I_pad]
+  float eps;
+  int T, d, H, G, dh, Kt, I_pad, splits;
+  int add;                 // ADD score instead of FO
+};
+// wcat[m][d + n] = sum_j wcat[m][j] w_o[j][n], m < rows (a multiple of 64), n < N.
+void launch_fold_f32(float* wcat, const float* w_o, int rows, int N, int d, int64_t ld, hipStream_t s);
+// Launches the fused kernel; returns the number of token splits used.
+int launch_affinity_f32(const AffinityF32Args& p, int cus, hipStream_t s);
+
 // ---- unit-mass fixed point (encode.cpp)
 dtp_status encode_unit_mass(const float* A, int64_t n, int64_t* Q);
 
