@@ -130,8 +130,9 @@ dtp_status dtp_affinity_accumulate_down(dtp_layer layer, const void* x, const vo
  *   B dev [G, I] float                          written
  * bf16: MFMA over d with gamma' * w^d_k rounded to bf16, fp32 sums of squares; requires
  * d and I multiples of 8.  f32: plain FMAs (small shapes).  Scratch of G*I*ceil((H/G+2)*dh
- * /128) floats, and for bf16 a gamma'-scaled transposed copy of W_down (I*d bf16), is taken
- * from the stream-ordered allocator and returned before exit. */
+ * /128) floats, and for bf16 copies of the scaled, transposed W_down and of the projections
+ * (about (I + (H + 2 G) dh) * d bf16, rounded up to whole tiles), is taken from the
+ * stream-ordered allocator and returned before exit. */
 dtp_status dtp_down_weights(int32_t d_model, int32_t n_neurons, int32_t n_q_heads,
                             int32_t n_kv_groups, int32_t head_dim, dtp_dtype dtype,
                             const void* w_q, const void* w_k, const void* w_v,

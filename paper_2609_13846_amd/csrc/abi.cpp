@@ -225,7 +225,7 @@ hipError_t stream_alloc(void** p, size_t bytes, hipStream_t s) {
     if (!retained[dev]) {
       hipMemPool_t pool;
       if (hipDeviceGetDefaultMemPool(&pool, dev) == hipSuccess) {
-        uint64_t keep = UINT64_MAX;
+        uint64_t keep = (uint64_t)1 << 30;
         (void)hipMemPoolSetAttribute(pool, hipMemPoolAttrReleaseThreshold, &keep);
       }
       retained[dev] = true;

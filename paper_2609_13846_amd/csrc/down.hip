@@ -11,9 +11,12 @@
 // then its k rows and its v rows, from the q_proj / k_proj / v_proj weight layouts.
 //
 // Kernels:
-//   scale_transpose_down_kernel  gamma' * W_down transposed to [I][d] bf16, once per call
-//   down_weight_bf16_kernel  one block per (128 neurons, 128 rows of W^{qkv}_g, group):
-//                            MFMA over d, then per-column sums of squares of the 128 rows
+//   scale_transpose_down_kernel  gamma' * W_down transposed to bf16 fragments, once per call
+//   qkv_fragments_kernel     the rows of every W^{qkv}_g as bf16 fragments, once per call
+//   down_weight_frag_kernel  one block per (256 neurons, 256 or 128 rows of W^{qkv}_g, group):
+//                            MFMA over d, then per-column sums of squares of each 128 rows
+//   down_weight_bf16_kernel  the same straight from the caller's matrices, for the
+//                            allocation-free call: 128 neurons x 128 rows per block
 //   down_weight_f32_kernel   the same with plain FMAs, one thread per (group, neuron)
 //   down_rows_reduce_kernel  B[g, k] = fixed-order fp64 sum over the row chunks
 //   down_combine_kernel      S_down[k, g] = s[k] B[g, k]
@@ -21,6 +24,7 @@
 #include <mutex>
 
 #include "dtp_internal.h"
+#include "frag_gemm.h"
 #include "tile_mfma.h"
 
 namespace dtp {
@@ -41,40 +45,129 @@ __device__ inline const T* qkv_row(const T* w_q, const T* w_k, const T* w_v, int
   return w_v + ((int64_t)g * dh + rho - dh) * d;
 }
 
-// tw[k][j] = bf16(w_down[j][k] * gamma'[j]): W_down scaled and transposed once per call, so
-// that the weight kernel reads each neuron's column contiguous along the contraction
-// instead of scaling and transposing it again for every group and row chunk.  64 x 64
-// tiles through LDS, reads along k and writes along j.
+// gamma' * W_down, transposed, in fragment-major layout (rows k < rows, a multiple of 64,
+// columns j < 32 ks): element (k, j) = bf16(w_down[j][k] * gamma'[j]), zeros past I and d.  Once
+// per call, so that the weight kernel's neuron operand is contiguous along the contraction.
+// 64 x 64 tiles through LDS, 16-byte reads along k (I % 8 == 0) and writes of whole
+// fragments.  HBM-bound: 40 us at the 8B-class shape (106 us with 2-byte accesses).
 __global__ void __launch_bounds__(256)
 scale_transpose_down_kernel(const uint16_t* __restrict__ w_down, const uint16_t* __restrict__ gamma,
-                            int d, int I, uint16_t* __restrict__ tw) {
-  __shared__ uint16_t tile[64][64 + 2];
+                            int d, int I, int ks, uint16_t* __restrict__ tw) {
+  __shared__ __attribute__((aligned(16))) uint16_t tile[64][64 + 8];
   const int k0 = blockIdx.x * 64, j0 = blockIdx.y * 64;
-  for (int idx = threadIdx.x; idx < 64 * 64; idx += 256) {
-    const int r = idx / 64, c = idx % 64;
+#pragma unroll
+  for (int pass = 0; pass < 2; ++pass) {
+    const int idx = threadIdx.x + 256 * pass;
+    const int r = idx / 8, c = 8 * (idx % 8);
     const int j = j0 + r, k = k0 + c;
-    tile[r][c] = j < d && k < I
-                     ? f32_to_bf16(bf16_to_f32(w_down[(int64_t)j * I + k]) * bf16_to_f32(gamma[j]))
-                     : (uint16_t)0;
+    u32x4 v = {0u, 0u, 0u, 0u};
+    if (j < d && k < I) {
+      v = *reinterpret_cast<const u32x4*>(w_down + (int64_t)j * I + k);
+      const float gj = bf16_to_f32(gamma[j]);
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        v[e] = (uint32_t)f32_to_bf16(__uint_as_float(v[e] << 16) * gj) |
+               ((uint32_t)f32_to_bf16(__uint_as_float(v[e] & 0xffff0000u) * gj) << 16);
+    }
+    *reinterpret_cast<u32x4*>(&tile[r][c]) = v;
   }
   __syncthreads();
-  for (int idx = threadIdx.x; idx < 64 * 64; idx += 256) {
-    const int r = idx / 64, c = idx % 64;
-    const int k = k0 + r, j = j0 + c;
-    if (k < I && j < d) tw[(int64_t)k * d + j] = tile[c][r];
+  // 4 x 2 fragments of 64 pieces: wavefront w writes those of rows 16 w .. + 15
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int k = 16 * w + lane % 16;
+#pragma unroll
+  for (int half = 0; half < 2; ++half) {
+    const int j = 32 * half + 8 * (lane / 16);
+    if (j0 + j >= 32 * ks) continue;
+    u32x4 o;
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      o[e] = (uint32_t)tile[j + 2 * e][k] | ((uint32_t)tile[j + 2 * e + 1][k] << 16);
+    *reinterpret_cast<u32x4*>(tw + frag_offset(k0 + k, j0 + j, ks)) = o;
+  }
+}
+
+// The rows of every W^{qkv}_g in fragment-major layout, each group padded with zero rows to
+// n_chunks chunks of `chunk_rows` (and zero columns past d, a multiple of 8).  One wavefront
+// per fragment: lane l reads piece l % 4 of row l / 4 (64 contiguous bytes per row) and the
+// pieces change lanes into fragment order.
+__global__ void __launch_bounds__(256)
+qkv_fragments_kernel(const uint16_t* __restrict__ w_q, const uint16_t* __restrict__ w_k,
+                     const uint16_t* __restrict__ w_v, int d, int hpg, int dh, int group_rows, int ks,
+                     int64_t n_frags, uint16_t* __restrict__ out) {
+  const int64_t f = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (f >= n_frags) return;  // whole wavefronts
+  const int lane = threadIdx.x & 63;
+  const int64_t rb = f / ks;
+  const int j = (int)(f % ks) * 32 + 8 * (lane % 4);
+  const int64_t row = rb * 16 + lane / 4;
+  const int g = (int)(row / group_rows), rho = (int)(row % group_rows);
+  u32x4 v = {0u, 0u, 0u, 0u};
+  if (rho < (hpg + 2) * dh && j < d)
+    v = *reinterpret_cast<const u32x4*>(qkv_row(w_q, w_k, w_v, g, rho, hpg, dh, d) + j);
+  const int from = (lane % 16) * 4 + lane / 16;
+  u32x4 o;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) o[e] = (uint32_t)__shfl((int)v[e], from, 64);
+  *reinterpret_cast<u32x4*>(out + (f * 64 + lane) * 8) = o;
+}
+
+// Column l % 16's sum of squares over the 32 rows of two stacked 16 x 16 accumulators.
+__device__ __forceinline__ float rows32_sum_sq(f32x4 lo, f32x4 hi) {
+  float c = 0.0f;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) c = fmaf(lo[e], lo[e], c);
+#pragma unroll
+  for (int e = 0; e < 4; ++e) c = fmaf(hi[e], hi[e], c);
+  c += __shfl_xor(c, 16, 64);
+  return c + __shfl_xor(c, 32, 64);
+}
+
+// partial[g][chunk][k] = sum over the chunk's 128 rows of (W^{qkv}_g[rho] . (gamma' * w^d_k))^2:
+// a block takes 32 AF rows (one chunk or two) of one group x 256 neurons.  The products'
+// order along the contraction and the order of the sums are those of
+// down_weight_bf16_kernel, so both give the same bits.  Bound by the matrix cores: 721 GFLOP
+// of the 8B-class shape in 540 us (1,336 TFLOP/s, where a large library product reaches
+// 1,386 and 1,344 blocks fill 5.25 rounds of 256 CUs), against 960 us for 128 x 128 tiles
+// staged through registers into a padded double buffer.
+template <int AF>
+__global__ void __launch_bounds__(512, 2)
+down_weight_frag_kernel(const uint16_t* __restrict__ qkv, const uint16_t* __restrict__ tw, int ks,
+                        int n_row_tiles, int n_col_tiles, int I, float* __restrict__ partial) {
+  using P = FragPipe<AF, 4>;
+  __shared__ __attribute__((aligned(16))) uint16_t s0[P::kSlot];
+  __shared__ __attribute__((aligned(16))) uint16_t s1[P::kSlot];
+  __shared__ __attribute__((aligned(16))) uint16_t s2[P::kSlot];
+  __shared__ __attribute__((aligned(16))) uint16_t s3[P::kSlot];
+  __shared__ float red[P::kARows / 32][P::kBRows];  // sums over 32 rows
+  int rt, ct;
+  frag_work(blockIdx.x, n_row_tiles, n_col_tiles, 6, rt, ct);
+  P p(qkv + (int64_t)rt * P::kARows * ks * 32, ks, tw + (int64_t)ct * P::kBRows * ks * 32, ks);
+  p.contract(s0, s1, s2, s3, ks);
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+#pragma unroll
+    for (int i = 0; i < AF; i += 2) {
+      const float c = rows32_sum_sq(p.acc[i][j], p.acc[i + 1][j]);
+      if (p.lane < 16) red[(p.wm * AF + i) / 2][(p.wn * 4 + j) * 16 + p.lane] = c;
+    }
+  __syncthreads();
+  for (int idx = threadIdx.x; idx < P::kARows / kDRows * P::kBRows; idx += 512) {
+    const int chunk = idx / P::kBRows, c = idx % P::kBRows, k = ct * P::kBRows + c;
+    if (k < I)
+      partial[((int64_t)rt * (P::kARows / kDRows) + chunk) * I + k] =
+          red[4 * chunk][c] + red[4 * chunk + 1][c] + red[4 * chunk + 2][c] + red[4 * chunk + 3][c];
   }
 }
 
 // partial[g][chunk][k] = sum over the chunk's rows rho of (W^{qkv}_g[rho] . (gamma' * w^d_k))^2.
-// TW: the B operand comes from scale_transpose_down_kernel's tw; otherwise each stage
-// scales and transposes its slice of W_down itself (the allocation-free path, which has no
-// room for tw).  Both fill the LDS tile with the same values, so B is the same to the bit.
-template <bool TW>
+// The allocation-free form: each stage scales and transposes its slice of W_down itself, for
+// want of room for a copy.
 __global__ void __launch_bounds__(kTileThreads)
 down_weight_bf16_kernel(const uint16_t* __restrict__ w_q, const uint16_t* __restrict__ w_k,
                         const uint16_t* __restrict__ w_v, const uint16_t* __restrict__ gamma,
-                        const uint16_t* __restrict__ w_down, const uint16_t* __restrict__ tw,
-                        int d, int I, int hpg, int dh, float* __restrict__ partial) {
+                        const uint16_t* __restrict__ w_down, int d, int I, int hpg, int dh,
+                        float* __restrict__ partial) {
   __shared__ __attribute__((aligned(16))) uint16_t As[2][kDRows * kDRow];
   __shared__ __attribute__((aligned(16))) uint16_t Bs[2][kDCols * kDRow];
   __shared__ float red[4][kDCols];
@@ -82,9 +175,7 @@ down_weight_bf16_kernel(const uint16_t* __restrict__ w_q, const uint16_t* __rest
   const int k0 = blockIdx.x * kDCols, chunk = blockIdx.y, g = blockIdx.z;
   const int n_chunks = gridDim.y;
   const int R = (hpg + 2) * dh;
-  f32x16 acc[4];
-#pragma unroll
-  for (int b = 0; b < 4; ++b) acc[b] = f32x16{};
+  f32x4 acc[2][8] = {};
   // A stage's operands in registers: A, 128 rows x 32 columns of W^{qkv}_g, and B, 128
   // neurons x 32 columns of gamma' * W_down, 16 bytes per thread and pass (2 passes each).
   // Stage kc+32 is fetched into registers during stage kc's MFMAs and stored into the
@@ -103,18 +194,12 @@ down_weight_bf16_kernel(const uint16_t* __restrict__ w_q, const uint16_t* __rest
 #pragma unroll
     for (int pass = 0; pass < 2; ++pass) {
       bv[pass] = u32x4{0u, 0u, 0u, 0u};
-      if constexpr (TW) {
-        const int row = threadIdx.x / 4 + 64 * pass, seg = threadIdx.x % 4;
-        const int k = k0 + row, j = kc + 8 * seg;
-        if (k < I && j < d) bv[pass] = *reinterpret_cast<const u32x4*>(tw + (int64_t)k * d + j);
-      } else {
-        const int idx = threadIdx.x + kTileThreads * pass;
-        const int jj = idx / 16, kseg = idx % 16;
-        const int j = kc + jj, k = k0 + 8 * kseg;
-        // I % 8 == 0: the 8 neurons are all valid or all past I
-        if (j < d && k < I) bv[pass] = *reinterpret_cast<const u32x4*>(w_down + (int64_t)j * I + k);
-        bg[pass] = j < d ? bf16_to_f32(gamma[j]) : 0.0f;
-      }
+      const int idx = threadIdx.x + kTileThreads * pass;
+      const int jj = idx / 16, kseg = idx % 16;
+      const int j = kc + jj, k = k0 + 8 * kseg;
+      // I % 8 == 0: the 8 neurons are all valid or all past I
+      if (j < d && k < I) bv[pass] = *reinterpret_cast<const u32x4*>(w_down + (int64_t)j * I + k);
+      bg[pass] = j < d ? bf16_to_f32(gamma[j]) : 0.0f;
     }
   };
   auto store = [&](int buf) __attribute__((always_inline)) {
@@ -125,17 +210,13 @@ down_weight_bf16_kernel(const uint16_t* __restrict__ w_q, const uint16_t* __rest
     }
 #pragma unroll
     for (int pass = 0; pass < 2; ++pass) {
-      if constexpr (TW) {
-        const int row = threadIdx.x / 4 + 64 * pass, seg = threadIdx.x % 4;
-        *reinterpret_cast<u32x4*>(Bs[buf] + row * kDRow + 8 * seg) = bv[pass];
-      } else {  // scaled by gamma'[j] and stored transposed, [k][j]
-        const int idx = threadIdx.x + kTileThreads * pass;
-        const int jj = idx / 16, kseg = idx % 16;
+      // scaled by gamma'[j] and stored transposed, [k][j]
+      const int idx = threadIdx.x + kTileThreads * pass;
+      const int jj = idx / 16, kseg = idx % 16;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const uint16_t w = (uint16_t)(bv[pass][e / 2] >> (16 * (e % 2)));
-          Bs[buf][(8 * kseg + e) * kDRow + jj] = f32_to_bf16(bf16_to_f32(w) * bg[pass]);
-        }
+      for (int e = 0; e < 8; ++e) {
+        const uint16_t w = (uint16_t)(bv[pass][e / 2] >> (16 * (e % 2)));
+        Bs[buf][(8 * kseg + e) * kDRow + jj] = f32_to_bf16(bf16_to_f32(w) * bg[pass]);
       }
     }
   };
@@ -145,18 +226,26 @@ down_weight_bf16_kernel(const uint16_t* __restrict__ w_q, const uint16_t* __rest
   for (int kc = 0, buf = 0; kc < d; kc += kDKC, buf ^= 1) {
     const bool more = kc + kDKC < d;
     if (more) fetch(kc + kDKC);
-    mfma_stage<kDKC>(As[buf], Bs[buf], acc, wave, lane);
+    const int at = (lane & 15) * kDRow + 8 * (lane >> 4);
+    bf16x8 a[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+      a[i] = *reinterpret_cast<const bf16x8*>(As[buf] + (32 * wave + 16 * i) * kDRow + at);
+#pragma unroll
+    for (int b = 0; b < 8; ++b) {
+      const bf16x8 bb = *reinterpret_cast<const bf16x8*>(Bs[buf] + 16 * b * kDRow + at);
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+        acc[i][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], bb, acc[i][b], 0, 0, 0);
+    }
     if (more) store(buf ^ 1);
     __syncthreads();
   }
   // Sum of squares over the wave's 32 rows, per column; rows past R are zero.
 #pragma unroll
-  for (int b = 0; b < 4; ++b) {
-    float c = 0.0f;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) c = fmaf(acc[b][i], acc[b][i], c);
-    c += __shfl_xor(c, 32, 64);
-    if (lane < 32) red[wave][b * 32 + lane] = c;
+  for (int b = 0; b < 8; ++b) {
+    const float c = rows32_sum_sq(acc[0][b], acc[1][b]);
+    if (lane < 16) red[wave][b * 16 + lane] = c;
   }
   __syncthreads();
   for (int c = threadIdx.x; c < kDCols; c += kTileThreads) {
@@ -291,47 +380,54 @@ dtp_status down_weights(int32_t d_model, int32_t n_neurons, int32_t n_q_heads, i
   DTP_CHECK(n_neurons % 8 == 0, DTP_ERR_INVALID_ARG, "n_neurons=%d is not a multiple of 8",
             n_neurons);
   float* partial = nullptr;
-  uint16_t* tw = nullptr;
+  hipError_t e = hipSuccess;
   if (use_static) {
     dtp_status st = noalloc_scratch(&partial);
     if (st != DTP_OK) return st;
-  } else {
-    DTP_HIP(hipMallocAsync((void**)&partial, sizeof(float) * (size_t)GI * n_chunks, s));
-    const hipError_t ea = hipMallocAsync((void**)&tw, sizeof(uint16_t) * (size_t)n_neurons * d_model, s);
-    if (ea != hipSuccess) {
-      (void)hipFreeAsync(partial, s);
-      DTP_HIP(ea);
-    }
-  }
-  dim3 grid((n_neurons + kDCols - 1) / kDCols, n_chunks, n_kv_groups);
-  hipError_t e = hipSuccess;
-  if (tw) {
-    const dim3 tg((n_neurons + 63) / 64, (d_model + 63) / 64);
-    scale_transpose_down_kernel<<<tg, 256, 0, s>>>((const uint16_t*)w_down,
-                                                   (const uint16_t*)gamma_next, d_model, n_neurons, tw);
-    e = hipGetLastError();
-    if (e == hipSuccess)
-      down_weight_bf16_kernel<true><<<grid, kTileThreads, 0, s>>>(
-          (const uint16_t*)w_q, (const uint16_t*)w_k, (const uint16_t*)w_v,
-          (const uint16_t*)gamma_next, (const uint16_t*)w_down, tw, d_model, n_neurons, hpg,
-          head_dim, partial);
-  } else {
-    down_weight_bf16_kernel<false><<<grid, kTileThreads, 0, s>>>(
+    const dim3 grid((n_neurons + kDCols - 1) / kDCols, n_chunks, n_kv_groups);
+    down_weight_bf16_kernel<<<grid, kTileThreads, 0, s>>>(
         (const uint16_t*)w_q, (const uint16_t*)w_k, (const uint16_t*)w_v,
-        (const uint16_t*)gamma_next, (const uint16_t*)w_down, nullptr, d_model, n_neurons, hpg,
-        head_dim, partial);
+        (const uint16_t*)gamma_next, (const uint16_t*)w_down, d_model, n_neurons, hpg, head_dim,
+        partial);
+    e = hipGetLastError();
+  } else {
+    // One block of scratch: [partial sums | neuron fragments | row fragments].
+    const int ks = (d_model + 31) / 32;
+    const int col_tiles = (n_neurons + 255) / 256;
+    const int64_t rows = (int64_t)n_kv_groups * n_chunks * kDRows;
+    const size_t part_bytes = (sizeof(float) * (size_t)GI * n_chunks + 1023) / 1024 * 1024;
+    const size_t tw_bytes = (size_t)col_tiles * 256 * ks * 64, qkv_bytes = (size_t)rows * ks * 64;
+    char* base = nullptr;
+    DTP_HIP(stream_alloc((void**)&base, part_bytes + tw_bytes + qkv_bytes, s));
+    partial = (float*)base;
+    uint16_t* tw = (uint16_t*)(base + part_bytes);
+    uint16_t* qkv = (uint16_t*)(base + part_bytes + tw_bytes);
+    const dim3 tg(col_tiles * 4, (ks + 1) / 2);
+    scale_transpose_down_kernel<<<tg, 256, 0, s>>>((const uint16_t*)w_down, (const uint16_t*)gamma_next,
+                                                   d_model, n_neurons, ks, tw);
+    const int64_t n_frags = rows / 16 * ks;
+    qkv_fragments_kernel<<<blocks_for(n_frags, 4), 256, 0, s>>>(
+        (const uint16_t*)w_q, (const uint16_t*)w_k, (const uint16_t*)w_v, d_model, hpg, head_dim,
+        n_chunks * kDRows, ks, n_frags, qkv);
+    // Two chunks per block where a group has an even number of them: half the neuron
+    // fragments read per product.
+    const int row_tiles = (int)(rows / (n_chunks % 2 == 0 ? 2 * kDRows : kDRows));
+    if (n_chunks % 2 == 0)
+      down_weight_frag_kernel<8><<<row_tiles * col_tiles, 512, 0, s>>>(qkv, tw, ks, row_tiles, col_tiles,
+                                                                       n_neurons, partial);
+    else
+      down_weight_frag_kernel<4><<<row_tiles * col_tiles, 512, 0, s>>>(qkv, tw, ks, row_tiles, col_tiles,
+                                                                       n_neurons, partial);
+    e = hipGetLastError();
   }
-  if (e == hipSuccess) e = hipGetLastError();
   if (e == hipSuccess) {
     down_rows_reduce_kernel<<<blocks_for(GI, 256), 256, 0, s>>>(partial, n_kv_groups, n_chunks,
                                                                 n_neurons, B);
     e = hipGetLastError();
   }
-  const hipError_t ef = use_static ? hipSuccess : hipFreeAsync(partial, s);
-  const hipError_t et = tw ? hipFreeAsync(tw, s) : hipSuccess;
+  const hipError_t ef = use_static ? hipSuccess : stream_free(partial, s);
   DTP_HIP(e);
   DTP_HIP(ef);
-  DTP_HIP(et);
   return DTP_OK;
 }
 
