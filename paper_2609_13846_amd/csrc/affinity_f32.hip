@@ -18,6 +18,7 @@ namespace {
 constexpr int kFK = 16;          // contraction depth of a stage: d and dh are multiples of it
 constexpr int kFRow = kFK + 4;   // floats per LDS row: 16 rows' 16-byte reads cover the 64 banks once
 constexpr int kFThreads = 256;
+constexpr int kMaxSplitsF32 = 128;  // token splits per launch (size of the partials)
 constexpr int kFTile = 64;       // neurons per tile of the folded rows (64 gate rows, then 64 up)
 
 typedef __attribute__((ext_vector_type(4))) float f32x4v;
@@ -264,10 +265,31 @@ affinity_f32_kernel(AffinityF32Args p) {
   }
 }
 
+// Token splits of a launch of `groups` neuron groups x `mtiles` token tiles.  Blocks of equal
+// length run in rounds of one per CU (several share a CU, and its matrix cores), a block
+// taking up to ceil(mtiles / S) tiles: the launch lasts about ceil(groups * S / CUs) *
+// ceil(mtiles / S) tile times.  From the smallest count that gives each CU three blocks, up
+// to four times it, the first that minimises that product.
+int choose_splits(int groups, int mtiles, int64_t cus) {
+  const int cap = std::min(mtiles, kMaxSplitsF32);
+  const int lo = std::max(1, std::min((int)((3 * cus + groups - 1) / groups), cap));
+  int best = lo;
+  int64_t best_cost = -1;
+  for (int s = lo; s <= std::min(4 * lo, cap); ++s) {
+    const int64_t rounds = ((int64_t)groups * s + cus - 1) / cus;
+    const int64_t cost = rounds * ((mtiles + s - 1) / s);
+    if (best_cost < 0 || cost < best_cost) {
+      best = s;
+      best_cost = cost;
+    }
+  }
+  return best;
+}
+
 template <int S>
-int launch_affinity_f32_tiles(AffinityF32Args p, hipStream_t s) {
+int launch_affinity_f32_tiles(AffinityF32Args p, int cus, hipStream_t s) {
   const int groups = p.I_pad / (2 * S);
-  p.splits = choose_splits(groups, (p.T + 2 * S - 1) / (2 * S));
+  p.splits = choose_splits(groups, (p.T + 2 * S - 1) / (2 * S), cus);
   const size_t shm = sizeof(float) * 4 * (p.G + 1) * S;
   affinity_f32_kernel<S><<<groups * p.splits, kFThreads, shm, s>>>(p);
   return p.splits;
@@ -281,7 +303,7 @@ void launch_fold_f32(float* wcat, const float* w_o, int rows, int N, int d, int6
 
 int launch_affinity_f32(const AffinityF32Args& p, int cus, hipStream_t s) {
   const int64_t tiles = (int64_t)(p.I_pad / 64) * ((p.T + 63) / 64);
-  return tiles < cus ? launch_affinity_f32_tiles<16>(p, s) : launch_affinity_f32_tiles<32>(p, s);
+  return tiles < cus ? launch_affinity_f32_tiles<16>(p, cus, s) : launch_affinity_f32_tiles<32>(p, cus, s);
 }
 
 }  // namespace dtp

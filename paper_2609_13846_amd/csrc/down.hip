@@ -11,7 +11,7 @@
 // then its k rows and its v rows, from the q_proj / k_proj / v_proj weight layouts.
 //
 // Kernels:
-//   scale_transpose_down_kernel  gamma' * W_down transposed to bf16 fragments, once per call
+//   transpose_fragments_kernel  gamma' * W_down transposed to bf16 fragments, once per call
 //   qkv_fragments_kernel     the rows of every W^{qkv}_g as bf16 fragments, once per call
 //   down_weight_frag_kernel  one block per (256 neurons, 256 or 128 rows of W^{qkv}_g, group):
 //                            MFMA over d, then per-column sums of squares of each 128 rows
@@ -22,6 +22,7 @@
 //   down_combine_kernel      S_down[k, g] = s[k] B[g, k]
 #include <cmath>
 #include <mutex>
+#include <type_traits>
 
 #include "dtp_internal.h"
 #include "frag_gemm.h"
@@ -34,6 +35,7 @@ constexpr int kDKC = 32;              // contraction depth per LDS stage
 constexpr int kDRow = kDKC + 8;       // bf16 per LDS row (16 bytes of padding)
 constexpr int kDRows = 128;           // rows of W^{qkv}_g per block (4 waves x 32)
 constexpr int kDCols = 128;           // neurons per block
+constexpr int kDThreads = 256;
 
 // Row rho of W^{qkv}_g inside the three projection matrices (each row d long).
 template <typename T>
@@ -45,52 +47,11 @@ __device__ inline const T* qkv_row(const T* w_q, const T* w_k, const T* w_v, int
   return w_v + ((int64_t)g * dh + rho - dh) * d;
 }
 
-// gamma' * W_down, transposed, in fragment-major layout (rows k < rows, a multiple of 64,
-// columns j < 32 ks): element (k, j) = bf16(w_down[j][k] * gamma'[j]), zeros past I and d.  Once
-// per call, so that the weight kernel's neuron operand is contiguous along the contraction.
-// 64 x 64 tiles through LDS, 16-byte reads along k (I % 8 == 0) and writes of whole
-// fragments.  HBM-bound: 40 us at the 8B-class shape (106 us with 2-byte accesses).
-__global__ void __launch_bounds__(256)
-scale_transpose_down_kernel(const uint16_t* __restrict__ w_down, const uint16_t* __restrict__ gamma,
-                            int d, int I, int ks, uint16_t* __restrict__ tw) {
-  __shared__ __attribute__((aligned(16))) uint16_t tile[64][64 + 8];
-  const int k0 = blockIdx.x * 64, j0 = blockIdx.y * 64;
-#pragma unroll
-  for (int pass = 0; pass < 2; ++pass) {
-    const int idx = threadIdx.x + 256 * pass;
-    const int r = idx / 8, c = 8 * (idx % 8);
-    const int j = j0 + r, k = k0 + c;
-    u32x4 v = {0u, 0u, 0u, 0u};
-    if (j < d && k < I) {
-      v = *reinterpret_cast<const u32x4*>(w_down + (int64_t)j * I + k);
-      const float gj = bf16_to_f32(gamma[j]);
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        v[e] = (uint32_t)f32_to_bf16(__uint_as_float(v[e] << 16) * gj) |
-               ((uint32_t)f32_to_bf16(__uint_as_float(v[e] & 0xffff0000u) * gj) << 16);
-    }
-    *reinterpret_cast<u32x4*>(&tile[r][c]) = v;
-  }
-  __syncthreads();
-  // 4 x 2 fragments of 64 pieces: wavefront w writes those of rows 16 w .. + 15
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int k = 16 * w + lane % 16;
-#pragma unroll
-  for (int half = 0; half < 2; ++half) {
-    const int j = 32 * half + 8 * (lane / 16);
-    if (j0 + j >= 32 * ks) continue;
-    u32x4 o;
-#pragma unroll
-    for (int e = 0; e < 4; ++e)
-      o[e] = (uint32_t)tile[j + 2 * e][k] | ((uint32_t)tile[j + 2 * e + 1][k] << 16);
-    *reinterpret_cast<u32x4*>(tw + frag_offset(k0 + k, j0 + j, ks)) = o;
-  }
-}
-
 // The rows of every W^{qkv}_g in fragment-major layout, each group padded with zero rows to
-// n_chunks chunks of `chunk_rows` (and zero columns past d, a multiple of 8).  One wavefront
-// per fragment: lane l reads piece l % 4 of row l / 4 (64 contiguous bytes per row) and the
-// pieces change lanes into fragment order.
+// group_rows (and zero columns past d, a multiple of 8).  One wavefront per fragment: lane l
+// reads piece l % 4 of row l / 4 (64 contiguous bytes per row) and the pieces change lanes
+// into fragment order.  Fragments in memory order: F of a stage, then the next stage's.
+template <int F>
 __global__ void __launch_bounds__(256)
 qkv_fragments_kernel(const uint16_t* __restrict__ w_q, const uint16_t* __restrict__ w_k,
                      const uint16_t* __restrict__ w_v, int d, int hpg, int dh, int group_rows, int ks,
@@ -98,9 +59,10 @@ qkv_fragments_kernel(const uint16_t* __restrict__ w_q, const uint16_t* __restric
   const int64_t f = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (f >= n_frags) return;  // whole wavefronts
   const int lane = threadIdx.x & 63;
-  const int64_t rb = f / ks;
-  const int j = (int)(f % ks) * 32 + 8 * (lane % 4);
-  const int64_t row = rb * 16 + lane / 4;
+  const int64_t tile = f / (F * ks);
+  const int at = (int)(f % (F * ks));
+  const int j = at / F * 32 + 8 * (lane % 4);
+  const int64_t row = (tile * F + at % F) * 16 + lane / 4;
   const int g = (int)(row / group_rows), rho = (int)(row % group_rows);
   u32x4 v = {0u, 0u, 0u, 0u};
   if (rho < (hpg + 2) * dh && j < d)
@@ -126,10 +88,10 @@ __device__ __forceinline__ float rows32_sum_sq(f32x4 lo, f32x4 hi) {
 // partial[g][chunk][k] = sum over the chunk's 128 rows of (W^{qkv}_g[rho] . (gamma' * w^d_k))^2:
 // a block takes 32 AF rows (one chunk or two) of one group x 256 neurons.  The products'
 // order along the contraction and the order of the sums are those of
-// down_weight_bf16_kernel, so both give the same bits.  Bound by the matrix cores: 721 GFLOP
-// of the 8B-class shape in 540 us (1,336 TFLOP/s, where a large library product reaches
-// 1,386 and 1,344 blocks fill 5.25 rounds of 256 CUs), against 960 us for 128 x 128 tiles
-// staged through registers into a padded double buffer.
+// down_weight_bf16_kernel, so both give the same bits.  Bound by the matrix cores and the clock
+// that they leave: 721 GFLOP of the 8B-class shape in 521 us (1,385 TFLOP/s, as much as a
+// large library product, at 1.90 GHz with the MFMAs busy 69% of the time and 1,344 blocks in
+// 5.25 rounds of 256 CUs), against 960 us for 128 x 128 tiles staged through registers.
 template <int AF>
 __global__ void __launch_bounds__(512, 2)
 down_weight_frag_kernel(const uint16_t* __restrict__ qkv, const uint16_t* __restrict__ tw, int ks,
@@ -142,7 +104,8 @@ down_weight_frag_kernel(const uint16_t* __restrict__ qkv, const uint16_t* __rest
   __shared__ float red[P::kARows / 32][P::kBRows];  // sums over 32 rows
   int rt, ct;
   frag_work(blockIdx.x, n_row_tiles, n_col_tiles, 6, rt, ct);
-  P p(qkv + (int64_t)rt * P::kARows * ks * 32, ks, tw + (int64_t)ct * P::kBRows * ks * 32, ks);
+  P p(qkv + (int64_t)rt * P::kARows * ks * 32, (uint32_t)P::kAFrags * ks * 1024u,
+      tw + (int64_t)ct * P::kBRows * ks * 32, (uint32_t)P::kBFrags * ks * 1024u);
   p.contract(s0, s1, s2, s3, ks);
 #pragma unroll
   for (int j = 0; j < 4; ++j)
@@ -163,7 +126,7 @@ down_weight_frag_kernel(const uint16_t* __restrict__ qkv, const uint16_t* __rest
 // partial[g][chunk][k] = sum over the chunk's rows rho of (W^{qkv}_g[rho] . (gamma' * w^d_k))^2.
 // The allocation-free form: each stage scales and transposes its slice of W_down itself, for
 // want of room for a copy.
-__global__ void __launch_bounds__(kTileThreads)
+__global__ void __launch_bounds__(kDThreads)
 down_weight_bf16_kernel(const uint16_t* __restrict__ w_q, const uint16_t* __restrict__ w_k,
                         const uint16_t* __restrict__ w_v, const uint16_t* __restrict__ gamma,
                         const uint16_t* __restrict__ w_down, int d, int I, int hpg, int dh,
@@ -194,7 +157,7 @@ down_weight_bf16_kernel(const uint16_t* __restrict__ w_q, const uint16_t* __rest
 #pragma unroll
     for (int pass = 0; pass < 2; ++pass) {
       bv[pass] = u32x4{0u, 0u, 0u, 0u};
-      const int idx = threadIdx.x + kTileThreads * pass;
+      const int idx = threadIdx.x + kDThreads * pass;
       const int jj = idx / 16, kseg = idx % 16;
       const int j = kc + jj, k = k0 + 8 * kseg;
       // I % 8 == 0: the 8 neurons are all valid or all past I
@@ -211,7 +174,7 @@ down_weight_bf16_kernel(const uint16_t* __restrict__ w_q, const uint16_t* __rest
 #pragma unroll
     for (int pass = 0; pass < 2; ++pass) {
       // scaled by gamma'[j] and stored transposed, [k][j]
-      const int idx = threadIdx.x + kTileThreads * pass;
+      const int idx = threadIdx.x + kDThreads * pass;
       const int jj = idx / 16, kseg = idx % 16;
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
@@ -248,7 +211,7 @@ down_weight_bf16_kernel(const uint16_t* __restrict__ w_q, const uint16_t* __rest
     if (lane < 16) red[wave][b * 16 + lane] = c;
   }
   __syncthreads();
-  for (int c = threadIdx.x; c < kDCols; c += kTileThreads) {
+  for (int c = threadIdx.x; c < kDCols; c += kDThreads) {
     const int k = k0 + c;
     if (k < I)
       partial[((int64_t)g * n_chunks + chunk) * I + k] = red[0][c] + red[1][c] + red[2][c] + red[3][c];
@@ -385,7 +348,7 @@ dtp_status down_weights(int32_t d_model, int32_t n_neurons, int32_t n_q_heads, i
     dtp_status st = noalloc_scratch(&partial);
     if (st != DTP_OK) return st;
     const dim3 grid((n_neurons + kDCols - 1) / kDCols, n_chunks, n_kv_groups);
-    down_weight_bf16_kernel<<<grid, kTileThreads, 0, s>>>(
+    down_weight_bf16_kernel<<<grid, kDThreads, 0, s>>>(
         (const uint16_t*)w_q, (const uint16_t*)w_k, (const uint16_t*)w_v,
         (const uint16_t*)gamma_next, (const uint16_t*)w_down, d_model, n_neurons, hpg, head_dim,
         partial);
@@ -403,21 +366,24 @@ dtp_status down_weights(int32_t d_model, int32_t n_neurons, int32_t n_q_heads, i
     uint16_t* tw = (uint16_t*)(base + part_bytes);
     uint16_t* qkv = (uint16_t*)(base + part_bytes + tw_bytes);
     const dim3 tg(col_tiles * 4, (ks + 1) / 2);
-    scale_transpose_down_kernel<<<tg, 256, 0, s>>>((const uint16_t*)w_down, (const uint16_t*)gamma_next,
+    transpose_fragments_kernel<16, true, true><<<tg, 256, 0, s>>>((const uint16_t*)w_down, (const uint16_t*)gamma_next,
                                                    d_model, n_neurons, ks, tw);
     const int64_t n_frags = rows / 16 * ks;
-    qkv_fragments_kernel<<<blocks_for(n_frags, 4), 256, 0, s>>>(
-        (const uint16_t*)w_q, (const uint16_t*)w_k, (const uint16_t*)w_v, d_model, hpg, head_dim,
-        n_chunks * kDRows, ks, n_frags, qkv);
     // Two chunks per block where a group has an even number of them: half the neuron
     // fragments read per product.
-    const int row_tiles = (int)(rows / (n_chunks % 2 == 0 ? 2 * kDRows : kDRows));
+    auto launch = [&](auto af) {
+      constexpr int AF = decltype(af)::value;
+      const int row_tiles = (int)(rows / (32 * AF));
+      qkv_fragments_kernel<2 * AF><<<blocks_for(n_frags, 4), 256, 0, s>>>(
+          (const uint16_t*)w_q, (const uint16_t*)w_k, (const uint16_t*)w_v, d_model, hpg, head_dim,
+          n_chunks * kDRows, ks, n_frags, qkv);
+      down_weight_frag_kernel<AF><<<row_tiles * col_tiles, 512, 0, s>>>(qkv, tw, ks, row_tiles, col_tiles,
+                                                                        n_neurons, partial);
+    };
     if (n_chunks % 2 == 0)
-      down_weight_frag_kernel<8><<<row_tiles * col_tiles, 512, 0, s>>>(qkv, tw, ks, row_tiles, col_tiles,
-                                                                       n_neurons, partial);
+      launch(std::integral_constant<int, 8>());
     else
-      down_weight_frag_kernel<4><<<row_tiles * col_tiles, 512, 0, s>>>(qkv, tw, ks, row_tiles, col_tiles,
-                                                                       n_neurons, partial);
+      launch(std::integral_constant<int, 4>());
     e = hipGetLastError();
   }
   if (e == hipSuccess) {

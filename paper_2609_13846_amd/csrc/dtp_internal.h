@@ -66,10 +66,8 @@ constexpr int kMantBits = 40;
 hipError_t stream_alloc(void** p, size_t bytes, hipStream_t s);
 hipError_t stream_free(void* p, hipStream_t s);
 
-// ---- launch shapes of the affinity kernels (affinity.hip): the current device's compute
-// units, and the token splits of a launch of `groups` neuron groups x `mtiles` token tiles.
+// ---- the current device's compute units (affinity.hip)
 int device_cus();
-int choose_splits(int groups, int mtiles);
 
 // ---- fp32 affinity path (affinity_f32.hip)
 struct AffinityF32Args {
