@@ -141,6 +141,8 @@ fold_kernel(uint16_t* wcat, const uint16_t* __restrict__ woT, int N, int dh, int
     const int n = ta * P::kARows + 16 * (p.wm * 8 + i) + 4 * (p.lane >> 4);
     if (n >= N) continue;  // a multiple of 16: whole fragments
     const int k = dP + n / dh * dhP + n % dh;
+    const bool last = n % dh / 16 == dh / 16 - 1;  // the fragment that ends its head
+    const int head_end = dP + (n / dh + 1) * dhP;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       const uint32_t m = (uint32_t)tb * P::kBRows + 16 * (p.wn * 4 + j) + (p.lane & 15);
@@ -148,6 +150,9 @@ fold_kernel(uint16_t* wcat, const uint16_t* __restrict__ woT, int N, int dh, int
       o.x = (uint32_t)f32_to_bf16(p.acc[i][j][0]) | ((uint32_t)f32_to_bf16(p.acc[i][j][1]) << 16);
       o.y = (uint32_t)f32_to_bf16(p.acc[i][j][2]) | ((uint32_t)f32_to_bf16(p.acc[i][j][3]) << 16);
       *reinterpret_cast<uint2*>(wcat + frag_offset<kWeightFrags>(m, k, ks) + k % 8) = o;
+      if (last)  // the zero columns up to the next head
+        for (int z = k + 16; z < head_end; z += 16)
+          *reinterpret_cast<uint2*>(wcat + frag_offset<kWeightFrags>(m, z, ks) + z % 8) = make_uint2(0u, 0u);
     }
   }
 }
@@ -1082,10 +1087,6 @@ dtp_status dtp_layer_create(const dtp_layer_desc* desc, dtp_layer* out) {
                                         std::min<int64_t>(pad_tokens(kTileTokens) + kSliceSpare * kTokenPad,
                                                           ((int64_t)1 << 30) / L->Kt / kTokenPad * kTokenPad));
       if (e == hipSuccess) e = hipMalloc(&L->w, 2 * rows * L->Kt);
-      if (e == hipSuccess && L->dhP != d.head_dim) {  // the columns between the heads, for good
-        e = hipMemset(L->w, 0, 2 * rows * L->Kt);
-        if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
-      }
       if (e == hipSuccess) e = hipMalloc(&L->woT, 2 * (size_t)((HD + 255) / 256 * 256) * L->dP);
       if (e == hipSuccess) e = hipMalloc(&L->xt, 2 * (size_t)L->tile_slice * L->Kt);
     } else {
