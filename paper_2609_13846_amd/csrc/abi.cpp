@@ -3,10 +3,13 @@
 // (Section 3, "Objective" and "Optimiser").  The affinity entry points live in
 // affinity.hip.
 #include <algorithm>
+#include <atomic>
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <exception>
 #include <mutex>
+#include <system_error>
 #include <thread>
 
 #include "dtp_internal.h"
@@ -194,6 +197,43 @@ class PinnedPool {
 PinnedPool& pinned_pool() {
   static PinnedPool* pool = new PinnedPool;  // lives until the process ends
   return *pool;
+}
+
+constexpr int kMaxSolverThreads = 16;
+constexpr size_t kEagerGainBytes = size_t(256) << 10;
+
+// Threads of a sweep's neuron step: one per 200 us of it, about what starting and joining one
+// costs several times over.  (An exact solution takes about 10 ns per neuron with two devices,
+// 15 per neuron and device with more.)
+int solver_threads(int N, int I, int L) {
+  const int64_t ns = (int64_t)N * I * (L == 2 ? 10 : 15 * L);
+  const int hw = (int)std::max(1u, std::thread::hardware_concurrency());
+  return (int)std::max<int64_t>(1, std::min<int64_t>({ns / 200000, kMaxSolverThreads, hw}));
+}
+
+// Runs `work` on n threads, this one among them.  A thread that cannot be started is done
+// without (the others take its share); what any of them throws is thrown here.
+template <typename F>
+void run_on_threads(int n, F&& work) {
+  std::mutex mu;
+  std::exception_ptr failed;
+  auto guarded_work = [&]() {
+    try {
+      work();
+    } catch (...) {
+      std::lock_guard<std::mutex> lock(mu);
+      failed = std::current_exception();
+    }
+  };
+  std::vector<std::thread> pool;
+  pool.reserve((size_t)n);
+  try {
+    for (int t = 1; t < n; ++t) pool.emplace_back(guarded_work);
+  } catch (const std::system_error&) {
+  }
+  guarded_work();
+  for (auto& th : pool) th.join();
+  if (failed) std::rethrow_exception(failed);
 }
 
 // A pinned block for one call, or (if pinned memory cannot be had) pageable memory.
@@ -439,32 +479,50 @@ dtp_status dtp_coordinate_ascent(int32_t N, int32_t G, int32_t I, int32_t L, con
       return st;
     hipStream_t s = (hipStream_t)stream;
 
-    // Unit-mass codes of every matrix, computed on the device where the head step reads
-    // them; the host copy feeds the neuron step and J.  Layout of the scratch block:
-    // [encode stats | Q_up | Q_down | nu].
+    // The codes stay on the device.  With two devices the neuron step runs there too, and only
+    // the head step's values (each layer's part of J) come back after a sweep; otherwise it
+    // runs on the host, from the gain matrices (M).  Device scratch, in this order, so that
+    // what is copied together is contiguous:
+    // [encode stats | M | value | nu | h | best | moves | neuron moves | Q_up | Q_down].
     const int nmat = N + (has_down ? N - 1 : 0);
-    const size_t st_bytes = sizeof(EncodeStats) * nmat;
-    const size_t qu_bytes = sizeof(int64_t) * nup, qd_bytes = sizeof(int64_t) * ndown;
+    const bool neurons = !opt.freeze_neurons;
+    const bool on_device = neurons && L == 2 && !opt.dual_ascent_neurons;
+    const bool on_host = neurons && !on_device;
+    auto up = [](size_t b) { return (b + 255) & ~size_t(255); };
+    const size_t st_bytes = up(sizeof(EncodeStats) * nmat);
+    // M, or the keys of the selection on the device
+    const size_t m_bytes = neurons ? up(sizeof(int64_t) * (size_t)N * I * (on_device ? 1 : L)) : 0;
+    const size_t value_bytes = up(sizeof(int64_t) * (size_t)N);
+    const size_t nu_bytes = up(sizeof(int32_t) * (size_t)N * I), h_bytes = up(sizeof(int32_t) * (size_t)N * G);
+    const size_t m_at = st_bytes, value_at = m_at + m_bytes, nu_at = value_at + 2 * value_bytes;
+    const size_t h_at = nu_at + nu_bytes, best_at = h_at + h_bytes, moves_at = best_at + value_bytes;
+    const size_t flags_at = moves_at + up((size_t)N), q_at = flags_at + up((size_t)N);
     DevBuf block(s);
-    DTP_HIP(stream_alloc(&block.p, st_bytes + qu_bytes + qd_bytes + sizeof(int32_t) * (size_t)N * I, s));
-    EncodeStats* st_dev = (EncodeStats*)block.p;
-    int64_t* qu_dev = (int64_t*)((char*)block.p + st_bytes);
-    int64_t* qd_dev = has_down ? qu_dev + nup : nullptr;
-    int32_t* nu_dev = (int32_t*)((char*)qu_dev + qu_bytes + qd_bytes);
+    DTP_HIP(stream_alloc(&block.p, q_at + sizeof(int64_t) * (nup + ndown), s));
+    char* const dev = (char*)block.p;
+    int64_t* const qu_dev = (int64_t*)(dev + q_at);
+    int64_t* const qd_dev = has_down ? qu_dev + nup : nullptr;
+    int64_t* const m_dev = (int64_t*)(dev + m_at);
     st = launch_encode_unit_mass(A_up, N, A_down, has_down ? N - 1 : 0, (int64_t)G * I, qu_dev,
-                                 qd_dev, st_dev, s);
+                                 qd_dev, (EncodeStats*)dev, s);
     if (st != DTP_OK) return st;
-    // Host mirror of [encode stats | Q_up | Q_down], then the staging of the uploaded nu and
-    // of the best ranks, in pinned memory: one copy brings the stats and codes back.
-    const size_t nu_bytes = sizeof(int32_t) * (size_t)N * I;
-    const size_t best_off = (st_bytes + qu_bytes + qd_bytes + nu_bytes + 7) / 8 * 8;
-    HostStaging host(best_off + sizeof(int64_t) * (size_t)N);
+    // The host mirror of all but the codes, in pinned memory.
+    HostStaging host(q_at);
     const EncodeStats* stats = (const EncodeStats*)host.base;
-    const int64_t* Qu = (const int64_t*)(host.base + st_bytes);
-    const int64_t* Qd = has_down ? Qu + nup : nullptr;
-    int32_t* nu_host = (int32_t*)(host.base + st_bytes + qu_bytes + qd_bytes);
-    const int64_t* best = (const int64_t*)(host.base + best_off);
-    DTP_HIP(hipMemcpyAsync(host.base, block.p, st_bytes + qu_bytes + qd_bytes, hipMemcpyDeviceToHost, s));
+    const int64_t* M = (const int64_t*)(host.base + m_at);
+    const int64_t* value = (const int64_t*)(host.base + value_at);  // of two sweeps
+    int32_t* const nus = (int32_t*)(host.base + nu_at);
+    int32_t* const hs = (int32_t*)(host.base + h_at);
+    uint8_t* const moves = (uint8_t*)(host.base + moves_at);
+    uint8_t* const flags = (uint8_t*)(host.base + flags_at);
+    // Contiguous start.
+    auto layer_moves = [&](int i) { return opt.layer_mask == nullptr || opt.layer_mask[i] != 0; };
+    for (int i = 0; i < N; ++i) {
+      for (int g = 0; g < G; ++g) hs[(size_t)i * G + g] = g / (G / L);
+      for (int k = 0; k < I; ++k) nus[(size_t)i * I + k] = k / (I / L);
+      flags[i] = layer_moves(i);
+      moves[i] = flags[i] && !opt.freeze_heads;
+    }
     // The partition table is enumerated and queued while the stream encodes.  Every return
     // below synchronises the stream before the guard releases the table's host copy.
     ScoreWorkspace ws;
@@ -478,77 +536,106 @@ dtp_status dtp_coordinate_ascent(int32_t N, int32_t G, int32_t I, int32_t L, con
       }
     } guard{&ws, s};
     if (st != DTP_OK) return st;
-    DTP_HIP(hipStreamSynchronize(s));
-    for (int m = 0; m < nmat; ++m) {
-      st = m < N ? check_encode_stats(stats[m], "up affinity of layer", m)
-                 : check_encode_stats(stats[m], "down affinity of layer", m - N);
-      if (st != DTP_OK) return st;
-    }
-    const std::vector<uint8_t>& table = ws.host_table;
-
-    // Contiguous start.
-    std::vector<int32_t> hs((size_t)N * G), nus((size_t)N * I);
-    for (int i = 0; i < N; ++i) {
-      for (int g = 0; g < G; ++g) hs[(size_t)i * G + g] = g / (G / L);
-      for (int k = 0; k < I; ++k) nus[(size_t)i * I + k] = k / (I / L);
-    }
-    auto moves = [&](int i) { return opt.layer_mask == nullptr || opt.layer_mask[i] != 0; };
+    ws.best = (int64_t*)(dev + best_at);
+    ws.value = (int64_t*)(dev + value_at);
+    ws.h = (int32_t*)(dev + h_at);
+    ws.moves = (const uint8_t*)(dev + moves_at);
     const bool minimise = opt.minimise != 0;
+    int32_t* const nu_dev = (int32_t*)(dev + nu_at);
+    const int minim = minimise ? 1 : 0;
+    auto neuron_block = [&]() {
+      return ws.two_device_neurons(ws, qu_dev, qd_dev, minim, (const uint8_t*)(dev + flags_at),
+                                   (uint64_t*)m_dev, nu_dev, s);
+    };
+    auto head_block = [&]() { return launch_partition_scores(ws, qu_dev, nu_dev, qd_dev, nu_dev, minim, s); };
+    auto gains = [&]() { return ws.neuron_gains(ws, qu_dev, qd_dev, minim, m_dev, s); };
+    auto total = [&](const int64_t* v) {
+      int64_t t = 0;
+      for (int i = 0; i < N; ++i) t += v[i];
+      return t;
+    };
+    auto check_stats = [&]() -> dtp_status {
+      for (int m = 0; m < nmat; ++m) {
+        const dtp_status e = m < N ? check_encode_stats(stats[m], "up affinity of layer", m)
+                                   : check_encode_stats(stats[m], "down affinity of layer", m - N);
+        if (e != DTP_OK) return e;
+      }
+      return DTP_OK;
+    };
     int64_t J_prev = 0;
     int sweep = 0;
-    while (sweep < opt.max_sweeps) {
-      ++sweep;
-      if (!opt.freeze_neurons) {
-        // Neuron block: layers are independent given the heads; solve them in parallel.
-        const unsigned hw = std::max(1u, std::thread::hardware_concurrency());
-        const int nthreads = (int)std::min<unsigned>(hw, (unsigned)N);
-        auto work = [&](int t) {
-          std::vector<int64_t> M;
-          for (int i = t; i < N; i += nthreads) {
-            if (!moves(i)) continue;
-            const bool dn = has_down && i + 1 < N;
-            neuron_gain(G, I, L, Qu + (size_t)i * G * I, hs.data() + (size_t)i * G,
-                        dn ? Qd + (size_t)i * I * G : nullptr,
-                        dn ? hs.data() + (size_t)(i + 1) * G : nullptr, minimise, &M);
-            if (opt.dual_ascent_neurons)
-              balanced_assign_dual_ascent(I, L, M.data(), kDualAscentIterations, kDualAscentDecay,
-                                          nus.data() + (size_t)i * I, nullptr);
-            else
-              balanced_assign_exact(I, L, M.data(), nus.data() + (size_t)i * I, nullptr);
-          }
-        };
-        if (nthreads == 1) {
-          work(0);
-        } else {
-          std::vector<std::thread> pool;
-          for (int t = 0; t < nthreads; ++t) pool.emplace_back(work, t);
-          for (auto& th : pool) th.join();
+    DTP_HIP(hipMemcpyAsync(dev + nu_at, host.base + nu_at, q_at - nu_at, hipMemcpyHostToDevice, s));
+    if (!on_host) {
+      // Every sweep on the device.  The first is followed by a second, so the two are queued
+      // together; J of each comes back with the layout that the last one left.  (Codes of a
+      // matrix that could not be encoded are whatever the scratch held: their sweeps end like
+      // any other, and the outcome is dropped.)
+      for (bool done = false; !done;) {
+        const int first = sweep, queued = sweep == 0 ? std::min(2, opt.max_sweeps) : 1;
+        for (int j = 0; j < queued; ++j, ++sweep) {
+          ws.value = (int64_t*)(dev + value_at + j * value_bytes);
+          if (neurons && (st = neuron_block()) != DTP_OK) return st;
+          if ((st = head_block()) != DTP_OK) return st;
         }
-      }
-      if (!opt.freeze_heads) {
-        // staged: the previous sweep's upload from nu_host ended at its synchronisation
-        std::memcpy(nu_host, nus.data(), nu_bytes);
-        DTP_HIP(hipMemcpyAsync(nu_dev, nu_host, nu_bytes, hipMemcpyHostToDevice, s));
-        st = launch_partition_scores(ws, qu_dev, nu_dev, qd_dev, nu_dev, minimise ? 1 : 0, s);
-        if (st != DTP_OK) return st;
-        DTP_HIP(hipMemcpyAsync((void*)best, ws.best, sizeof(int64_t) * N, hipMemcpyDeviceToHost, s));
+        if (first == 0) DTP_HIP(hipMemcpyAsync(host.base, dev, st_bytes, hipMemcpyDeviceToHost, s));
+        DTP_HIP(hipMemcpyAsync(host.base + value_at, dev + value_at, best_at - value_at, hipMemcpyDeviceToHost, s));
         DTP_HIP(hipStreamSynchronize(s));
-        for (int i = 0; i < N; ++i) {
-          if (!moves(i)) continue;
-          DTP_CHECK(best[i] >= 0 && best[i] < P, DTP_ERR_HIP, "partition scoring returned rank %lld",
-                    (long long)best[i]);
-          for (int g = 0; g < G; ++g) hs[(size_t)i * G + g] = table[(size_t)best[i] * G + g];
+        if (first == 0 && (st = check_stats()) != DTP_OK) return st;
+        for (int j = 0; j < queued; ++j) {
+          const int64_t Jc = total((const int64_t*)((const char*)value + j * value_bytes));
+          done = first + j + 1 >= opt.max_sweeps ||
+                 (first + j > 0 && !(minimise ? Jc < J_prev : Jc > J_prev));
+          J_prev = Jc;
         }
       }
-      const int64_t Jc = objective_int(N, G, I, Qu, Qd, has_down, hs.data(), nus.data());
-      const bool improved = sweep == 1 || (minimise ? Jc < J_prev : Jc > J_prev);
-      J_prev = Jc;
-      if (!improved) break;
+    } else {
+      if ((st = gains()) != DTP_OK) return st;
+      DTP_HIP(hipMemcpyAsync(host.base, dev, st_bytes + m_bytes, hipMemcpyDeviceToHost, s));
+      DTP_HIP(hipStreamSynchronize(s));
+      if ((st = check_stats()) != DTP_OK) return st;
+      while (sweep < opt.max_sweeps) {
+        ++sweep;
+        {
+          // Neuron block: layers are independent given the heads; solve them in parallel, each
+          // thread the next layer that none has taken.
+          std::atomic<int> next{0};
+          auto work = [&]() {
+            for (int i = next++; i < N; i = next++) {
+              if (flags[i] == 0) continue;
+              const int64_t* Mi = M + (size_t)i * I * L;
+              int32_t* nu_i = nus + (size_t)i * I;
+              if (opt.dual_ascent_neurons)
+                balanced_assign_dual_ascent(I, L, Mi, kDualAscentIterations, kDualAscentDecay, nu_i, nullptr);
+              else
+                balanced_assign_exact(I, L, Mi, nu_i, nullptr);
+            }
+          };
+          run_on_threads(std::min(N, opt.dual_ascent_neurons ? kMaxSolverThreads : solver_threads(N, I, L)), work);
+        }
+        // Head block, then (the heads on the device already moved) the next sweep's gains: always
+        // after the first sweep, which another follows, and later where the copy costs no more
+        // than the round trip that it saves.
+        const bool more = sweep < opt.max_sweeps && (sweep == 1 || m_bytes <= kEagerGainBytes);
+        DTP_HIP(hipMemcpyAsync(dev + nu_at, nus, nu_bytes, hipMemcpyHostToDevice, s));
+        if ((st = head_block()) != DTP_OK) return st;
+        if (more && (st = gains()) != DTP_OK) return st;
+        const size_t from = more ? m_at : value_at;
+        DTP_HIP(hipMemcpyAsync(host.base + from, dev + from, nu_at - from, hipMemcpyDeviceToHost, s));
+        DTP_HIP(hipMemcpyAsync(host.base + h_at, dev + h_at, h_bytes, hipMemcpyDeviceToHost, s));
+        DTP_HIP(hipStreamSynchronize(s));
+        const int64_t Jc = total(value);
+        const bool improved = sweep == 1 || (minimise ? Jc < J_prev : Jc > J_prev);
+        J_prev = Jc;
+        if (!improved) break;
+        if (!more && sweep < opt.max_sweeps) {
+          if ((st = gains()) != DTP_OK) return st;
+          DTP_HIP(hipMemcpyAsync(host.base + m_at, dev + m_at, m_bytes, hipMemcpyDeviceToHost, s));
+          DTP_HIP(hipStreamSynchronize(s));
+        }
+      }
     }
-    // The uploads read host memory that is released on return.
-    DTP_HIP(hipStreamSynchronize(s));
-    std::memcpy(h, hs.data(), sizeof(int32_t) * hs.size());
-    std::memcpy(nu, nus.data(), sizeof(int32_t) * nus.size());
+    std::memcpy(h, hs, sizeof(int32_t) * (size_t)N * G);
+    std::memcpy(nu, nus, sizeof(int32_t) * (size_t)N * I);
     *J_fixed = J_prev;
     *J = (double)J_prev / (double)(int64_t(1) << kFracBits);
     *sweeps = sweep;

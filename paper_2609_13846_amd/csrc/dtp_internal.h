@@ -129,6 +129,24 @@ struct ScoreWorkspace {
   int64_t* C = nullptr;       // dev [N][G][L]
   int64_t* scores = nullptr;  // dev [N][P]
   int64_t* best = nullptr;    // dev [N]
+  // Set by the coordinate ascent, or NULL.  With them the scoring also applies its result: a
+  // layer whose `moves` is not 0 takes its best partition as its row of h, and value becomes
+  // the score of the partition that the layer has then (rank 0, the contiguous one, where it
+  // does not move).  The values of all layers sum to J, every edge once.
+  const uint8_t* moves = nullptr;  // dev [N]
+  int32_t* h = nullptr;            // dev [N][G]
+  int64_t* value = nullptr;        // dev [N]
+  // The gain matrices of the neuron step, M[i][k][l] = sum_{g: h_i(g)=l} Q_up[i][g][k] +
+  // sum_{g: h_{i+1}(g)=l} Q_down[i][k][g], negated with `minimise`; M dev [N][I][L], from this
+  // workspace's h.  Set by score_workspace_create.
+  dtp_status (*neuron_gains)(const ScoreWorkspace& ws, const int64_t* Q_up, const int64_t* Q_down,
+                             int minimise, int64_t* M, hipStream_t stream) = nullptr;
+  // The neuron step itself for two devices (L = 2), from this workspace's h: the canonical
+  // optimum of every layer whose `moves` (dev [N], not the workspace's) is not 0 into nu dev
+  // [N][I]; scratch dev [N][I].  Set by score_workspace_create.
+  dtp_status (*two_device_neurons)(const ScoreWorkspace& ws, const int64_t* Q_up, const int64_t* Q_down,
+                                   int minimise, const uint8_t* moves, uint64_t* scratch, int32_t* nu,
+                                   hipStream_t stream) = nullptr;
 };
 dtp_status score_workspace_create(ScoreWorkspace* ws, int N, int G, int I, int L, hipStream_t s);
 void score_workspace_destroy(ScoreWorkspace* ws);
