@@ -47,8 +47,7 @@ constexpr int kCols = 2 * kBN;    // its rows: 64 gate | 64 up
 constexpr int kStage = 32;        // contraction columns per stage of the bf16 kernels
 constexpr int kBlockNeurons = 128;     // neurons per block of the fused bf16 kernel
 constexpr int kWeightFrags = 2 * kBlockNeurons / 16;  // fragments per tile of weight rows
-constexpr int kTokenFrags = 12;        // fragments per tile of token rows
-constexpr int kTokenPad = 16 * kTokenFrags;  // token rows of a slice are padded to whole tiles
+constexpr int kTokenPad = 192;         // token rows per tile of long slices (choose_launch)
 constexpr int kSliceTokens = 1 << 18;  // tokens per internal slice (size of the 1/r buffer)
 constexpr int kMaxSplits = 128;        // token splits per launch (size of the partials)
 constexpr int kTileTokens = 1 << 15;   // tokens per bf16 slice (size of the tiled token buffer),
@@ -277,7 +276,7 @@ __device__ __forceinline__ uint32_t scale_bf16_pair(uint32_t w, float f) {
   return (__float_as_uint(lo) >> 16) | (__float_as_uint(hi) & 0xffff0000u);
 }
 
-template <int RUN, bool PAD>
+template <int F, int RUN, bool PAD>
 __global__ void __launch_bounds__(256)
 tile_tokens_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ attn,
                    const float* __restrict__ rinv, int T, int d, int HD, int dh, int dP, int dhP,
@@ -307,7 +306,7 @@ tile_tokens_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ 
       }
     }
   }
-  *reinterpret_cast<u32x4*>(xt + frag_offset<kTokenFrags>(t, k, ks)) = v;
+  *reinterpret_cast<u32x4*>(xt + frag_offset<F>(t, k, ks)) = v;
 }
 
 // ------------------------------------------------------------------ fused affinity (bf16)
@@ -613,7 +612,7 @@ affinity_bf16_kernel(AffinityArgs p) {
   const int tiles = (int)((int64_t)(split + 1) * p.mtiles / p.splits) - mt_begin;  // >= 1: splits <= mtiles
   {
     const uint32_t tile_bytes = (uint32_t)Pipe::kAFrags * p.ks * 1024u;
-    static_assert(Pipe::kAFrags == kTokenFrags && Pipe::kBFrags == kWeightFrags, "tiles as laid out");
+    static_assert(Pipe::kBFrags == kWeightFrags, "tiles as laid out");
     Block b{Pipe(p.xt + (int64_t)mt_begin * kRows * p.ks * kStage, (uint32_t)tiles * tile_bytes,
                  p.wcat + (int64_t)tg * Pipe::kBRows * p.ks * kStage, (uint32_t)Pipe::kBFrags * p.ks * 1024u)};
     const int heads = (g1 - g0) * p.hpg;
@@ -691,9 +690,10 @@ affinity_bf16_kernel(AffinityArgs p) {
   }
 }
 
-// Token rows of a slice rounded up to whole tiles.
-int64_t pad_tokens(int64_t T) { return (T + kTokenPad - 1) / kTokenPad * kTokenPad; }
+// Token rows rounded up to whole tiles.
+int64_t pad_tokens(int64_t T, int tile = kTokenPad) { return (T + tile - 1) / tile * tile; }
 
+template <int F>
 void launch_tile_tokens(const uint16_t* x, const uint16_t* attn, const float* rinv, int T, int T_pad, int d,
                         int H, int dh, int dP, int dhP, uint16_t* xt, hipStream_t s) {
   const int Kt = dP + H * dhP, HD = H * dh, ks = Kt / kStage;
@@ -701,11 +701,11 @@ void launch_tile_tokens(const uint16_t* x, const uint16_t* attn, const float* ri
   const unsigned grid = (n + 255) / 256;
   const bool pad = dP != d || dhP != dh;
   if (Kt % 64 == 0 && !pad)
-    tile_tokens_kernel<8, false><<<grid, 256, 0, s>>>(x, attn, rinv, T, d, HD, dh, dP, dhP, Kt / 64, n, ks, xt);
+    tile_tokens_kernel<F, 8, false><<<grid, 256, 0, s>>>(x, attn, rinv, T, d, HD, dh, dP, dhP, Kt / 64, n, ks, xt);
   else if (!pad)
-    tile_tokens_kernel<4, false><<<grid, 256, 0, s>>>(x, attn, rinv, T, d, HD, dh, dP, dhP, ks, n, ks, xt);
+    tile_tokens_kernel<F, 4, false><<<grid, 256, 0, s>>>(x, attn, rinv, T, d, HD, dh, dP, dhP, ks, n, ks, xt);
   else
-    tile_tokens_kernel<4, true><<<grid, 256, 0, s>>>(x, attn, rinv, T, d, HD, dh, dP, dhP, ks, n, ks, xt);
+    tile_tokens_kernel<F, 4, true><<<grid, 256, 0, s>>>(x, attn, rinv, T, d, HD, dh, dP, dhP, ks, n, ks, xt);
 }
 
 void launch_prep_gate_up(const uint16_t* w_gate, const uint16_t* w_up, const uint16_t* gamma, int I, int d,
@@ -741,41 +741,56 @@ int device_cus() {
 namespace {
 
 struct LaunchShape {
-  int splits = 1, hsplits = 1;
+  int tile = kTokenPad;  // token rows per tile: 192, 128 or 64
+  int mtiles = 1, splits = 1, hsplits = 1;
   int64_t cost = -1;
 };
 
-// Token splits and ranges of KV groups of a launch.  A CU runs one block at a time, and blocks
-// go to CUs as these become free.  The splits' lengths differ by one tile at most: with R
-// blocks per CU, rounded up, of f tiles and as many CUs' worth of them of one more, the launch
+// Tile height, token splits and ranges of KV groups of a launch.  A CU runs one block at a time,
+// and blocks go to CUs as these become free.  The splits' lengths differ by one tile at most: with
+// R blocks per CU, rounded up, of f tiles and as many CUs' worth of them of one more, the launch
 // lasts about R f + (longer blocks / CUs, rounded up) tiles and R starts and ends of a block,
 // about 12 stages each.  (4,080 tiles
 // of a Qwen3-0.6B-shaped slice: 16 tile times in 32 splits, 1,106 us; 128 splits of one or two
 // tiles, 22 by this measure, took 1,384.)  Splitting the groups repeats the
 // operating point in every range, so it is weighed only where the tiles alone do not give
 // each CU two.
-LaunchShape choose_launch(const AffinityArgs& p, bool add, int mtiles) {
+//
+// A stage of 192, 128 and 64 tokens takes about 24 : 19 : 15 (one tile of 64 tokens of a
+// Qwen3-0.6B-shaped layer: launches of 30, 25 and 20 us; 16,384 tokens: 550 us in tiles of 192
+// and 571 in tiles of 128), so the low tiles are for slices that fill few CUs or whose last
+// tile would be mostly padding.  1,000 tokens: 59, 49 and 64 us; with ADD 39, 35 and 43; 256
+// tokens of an 8B-class layer, bound by its weights' way from HBM: 170, 153 and 257.  In heads of
+// three, five and six stages the highest tile spills registers between its heads (1,500 and
+// 5,000 tokens, 12 heads of 80: 57 and 155 us, against 69 and 139 in tiles of 128).
+LaunchShape choose_launch(const AffinityArgs& p, bool add, int T, int64_t max_rows) {
   const int64_t cus = device_cus(), groups = p.I_pad / kBlockNeurons;
   const int n1 = add ? 0 : p.nq1 + 8;  // the operating point's epilogue: about 8 stages
   LaunchShape best;
-  auto weigh = [&](int s, int hs) {
+  auto weigh = [&](int tile, int stage_cost, int mtiles, int s, int hs) {
     const int64_t rounds = (groups * s * hs + cus - 1) / cus;
     const int64_t tiles = rounds * (mtiles / s) + (groups * hs * (mtiles % s) + cus - 1) / cus;
     const int heads = (p.G + hs - 1) / hs * p.hpg;
     const int64_t stages = n1 + (heads * p.nqh + 3) / 4 * 4;
-    const int64_t cost = tiles * stages + rounds * 12;
-    if (best.cost < 0 || cost < best.cost) best = {s, hs, cost};
+    const int64_t cost = (tiles * stages + rounds * 12) * stage_cost;
+    if (best.cost < 0 || cost < best.cost) best = {tile, mtiles, s, hs, cost};
   };
-  const int cap = std::min(mtiles, kMaxSplits);
-  for (int s = 1; s <= cap; ++s) weigh(s, 1);
-  if (groups * mtiles < 2 * cus)
-    for (int hs = 2; hs <= p.G; ++hs) weigh(cap, hs);
+  auto weigh_tile = [&](int tile, int stage_cost) {
+    if (pad_tokens(T, tile) > max_rows) return;
+    const int mtiles = (T + tile - 1) / tile, cap = std::min(mtiles, kMaxSplits);
+    for (int s = 1; s <= cap; ++s) weigh(tile, stage_cost, mtiles, s, 1);
+    if (groups * mtiles < 2 * cus)
+      for (int hs = 2; hs <= p.G; ++hs) weigh(tile, stage_cost, mtiles, cap, hs);
+  };
+  weigh_tile(192, p.nqh == 3 || p.nqh == 5 || p.nqh == 6 ? 26 : 24);
+  weigh_tile(128, 19);
+  weigh_tile(64, 15);
   return best;
 }
 
 template <int AF, bool ADD, bool DOWN>
-void launch_affinity_tiles(AffinityArgs p, const LaunchShape& l, int mtiles, hipStream_t s) {
-  p.mtiles = mtiles;
+void launch_affinity_tiles(AffinityArgs p, const LaunchShape& l, hipStream_t s) {
+  p.mtiles = l.mtiles;
   p.splits = l.splits;
   p.hsplits = l.hsplits;
   const int rows = (p.G + l.hsplits - 1) / l.hsplits + 1;
@@ -795,17 +810,14 @@ void launch_affinity_tiles(AffinityArgs p, const LaunchShape& l, int mtiles, hip
   }
 }
 
-// Launches the fused kernel on one slice of T tokens; returns the number of token splits.
-int launch_affinity_bf16(const AffinityArgs& p, int T, bool add, hipStream_t s) {
-  const int mtiles = (T + kTokenPad - 1) / kTokenPad;
-  const LaunchShape l = choose_launch(p, add, mtiles);
+template <int AF>
+void launch_affinity(const AffinityArgs& p, const LaunchShape& l, bool add, hipStream_t s) {
   if (add)
-    launch_affinity_tiles<6, true, false>(p, l, mtiles, s);
+    launch_affinity_tiles<AF, true, false>(p, l, s);
   else if (p.rinv_next)
-    launch_affinity_tiles<6, false, true>(p, l, mtiles, s);
+    launch_affinity_tiles<AF, false, true>(p, l, s);
   else
-    launch_affinity_tiles<6, false, false>(p, l, mtiles, s);
-  return l.splits;
+    launch_affinity_tiles<AF, false, false>(p, l, s);
 }
 
 // A[g][k] += sum_s partial[s][g][k] for g < G (row g = blockIdx.y), and s_down[k] +=
@@ -970,14 +982,29 @@ dtp_status accumulate(dtp_layer L, const void* x, const void* attn, const void* 
     const char* as = (const char*)attn + esz * (size_t)t0 * HD;
     const char* xns = x_next ? (const char*)x_next + esz * (size_t)t0 * dm : nullptr;
     const float* rinv_next = xns ? L->rinv_next : nullptr;
+    AffinityArgs p{};
+    LaunchShape shape;
     if (d.dtype == DTP_BF16) {
-      const int T_pad = (int)pad_tokens(T);
+      p.xt = L->xt;
+      p.wcat = (const uint16_t*)L->w;
+      p.rinv = L->rinv;
+      p.rinv_next = rinv_next;
+      p.nd = L->nd;
+      p.partial = L->partial;
+      p.ks = L->Kt / kStage;
+      p.nq1 = L->dP / kStage;
+      p.nqh = L->dhP / kStage;
+      p.G = G;
+      p.hpg = H / G;
+      p.I_pad = L->I_pad;
+      shape = choose_launch(p, add, T, L->tile_slice);
+      const int T_pad = shape.mtiles * shape.tile;
       const unsigned rb = (unsigned)((T_pad + 3) / 4);
       rms_kernel<uint16_t><<<rb, 256, 0, s>>>((const uint16_t*)xs, T, T_pad, dm, d.rms_eps, L->rinv);
       if (xns)
         rms_kernel<uint16_t><<<rb, 256, 0, s>>>((const uint16_t*)xns, T, T_pad, dm, eps_next, L->rinv_next);
-      launch_tile_tokens((const uint16_t*)xs, (const uint16_t*)as, L->rinv, T, T_pad, dm, H, dh, L->dP,
-                         L->dhP, L->xt, s);
+      (shape.tile == 64 ? launch_tile_tokens<4> : shape.tile == 128 ? launch_tile_tokens<8> : launch_tile_tokens<12>)(
+          (const uint16_t*)xs, (const uint16_t*)as, L->rinv, T, T_pad, dm, H, dh, L->dP, L->dhP, L->xt, s);
     } else if (xns) {  // the fp32 kernel takes 1/r from the rows that it stages
       rms_kernel<float><<<(unsigned)((T + 3) / 4), 256, 0, s>>>((const float*)xns, T, T, dm, eps_next,
                                                                 L->rinv_next);
@@ -992,39 +1019,28 @@ dtp_status accumulate(dtp_layer L, const void* x, const void* attn, const void* 
       DTP_HIP(hipEventRecord(e0, s));
     }
     if (d.dtype == DTP_BF16) {
-      AffinityArgs p{};
-      p.xt = L->xt;
-      p.wcat = (const uint16_t*)L->w;
-      p.rinv = L->rinv;
-      p.rinv_next = rinv_next;
-      p.nd = L->nd;
-      p.partial = L->partial;
-      p.ks = L->Kt / kStage;
-      p.nq1 = L->dP / kStage;
-      p.nqh = L->dhP / kStage;
-      p.G = G;
-      p.hpg = H / G;
-      p.I_pad = L->I_pad;
-      splits = launch_affinity_bf16(p, T, add, s);
+      (shape.tile == 64 ? launch_affinity<2> : shape.tile == 128 ? launch_affinity<4> : launch_affinity<6>)(
+          p, shape, add, s);
+      splits = shape.splits;
     } else {
-      AffinityF32Args p;
-      p.x = (const float*)xs;
-      p.attn = (const float*)as;
-      p.wcat = (const float*)L->w;
-      p.rinv_next = rinv_next;
-      p.nd = L->nd;
-      p.partial = L->partial;
-      p.eps = d.rms_eps;
-      p.T = T;
-      p.d = dm;
-      p.H = H;
-      p.G = G;
-      p.dh = dh;
-      p.Kt = L->Kt;
-      p.I_pad = L->I_pad;
-      p.splits = 0;
-      p.add = add ? 1 : 0;
-      splits = launch_affinity_f32(p, device_cus(), s);
+      AffinityF32Args f;
+      f.x = (const float*)xs;
+      f.attn = (const float*)as;
+      f.wcat = (const float*)L->w;
+      f.rinv_next = rinv_next;
+      f.nd = L->nd;
+      f.partial = L->partial;
+      f.eps = d.rms_eps;
+      f.T = T;
+      f.d = dm;
+      f.H = H;
+      f.G = G;
+      f.dh = dh;
+      f.Kt = L->Kt;
+      f.I_pad = L->I_pad;
+      f.splits = 0;
+      f.add = add ? 1 : 0;
+      splits = launch_affinity_f32(f, device_cus(), s);
     }
     DTP_HIP(hipGetLastError());
     if (L->profiling) {

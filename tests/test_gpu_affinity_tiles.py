@@ -36,6 +36,12 @@ pytestmark = pytest.mark.gpu
     (30000, "down", dict(d_model=48, n_neurons=1500, n_q_heads=3, n_kv_groups=3, head_dim=32)),  # tiles per block
     (75000, "down", dict(d_model=32, n_neurons=300, n_q_heads=2, n_kv_groups=1, head_dim=16)),  # three slices
     (75000, "add", dict(d_model=32, n_neurons=300, n_q_heads=3, n_kv_groups=3, head_dim=64)),
+] + [  # tiles of 128 and of 192 tokens in heads of each number of stages, as the sizes of a launch choose them
+    # (rounding W' and F to bf16 alone, in fp64, takes entries off by up to 1.1e-2 with d = 32, 7e-3 with 128)
+    (T, score, dict(d_model=256, n_neurons=I, n_q_heads=3, n_kv_groups=3, head_dim=dh))
+    for T, I in ((1000, 4096), (18400, 1024))
+    for dh, score in ((32, "fo"), (64, "down"), (96, "add"), (96, "down"), (128, "fo"), (160, "down"), (192, "add"),
+                      (256, "down"))
 ])
 def test_affinity_dispatch_edges(T, score, shape):
     import torch
