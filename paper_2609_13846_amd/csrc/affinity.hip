@@ -319,6 +319,7 @@ struct AffinityArgs {
   float* partial;         // [splits][G+1][I_pad]: G up rows, then the down statistic
   int ks, nq1, nqh;       // stages per row, of the operating point, per head
   int G, hpg, mtiles, splits, hsplits, I_pad;
+  int first;              // splits whose blocks come before those of the others
 };
 
 typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
@@ -602,14 +603,21 @@ affinity_bf16_kernel(AffinityArgs p) {
 
   int split, item;
   const int groups = p.I_pad / kBlockNeurons;
-  frag_work(blockIdx.x, p.splits, groups * p.hsplits, 4, split, item);
+  const int items = groups * p.hsplits, first = p.first * items;
+  if ((int)blockIdx.x < first) {
+    frag_work(blockIdx.x, p.first, items, 4, split, item);
+  } else {
+    frag_work(blockIdx.x - first, p.splits - p.first, items, 4, split, item);
+    split += p.first;
+  }
   const int tg = item / p.hsplits, hs = item % p.hsplits;
   const int g0 = hs * p.G / p.hsplits, g1 = (hs + 1) * p.G / p.hsplits;  // KV groups of this block
   const int rows = g1 - g0 + 1;
   for (int i = threadIdx.x; i < 8 * rows * 32; i += 512) banks[i] = 0.0f;
 
-  const int mt_begin = (int)((int64_t)split * p.mtiles / p.splits);
-  const int tiles = (int)((int64_t)(split + 1) * p.mtiles / p.splits) - mt_begin;  // >= 1: splits <= mtiles
+  const int longer = p.mtiles % p.splits;  // splits 0 .. longer - 1 have a tile more
+  const int mt_begin = split * (p.mtiles / p.splits) + min(split, longer);
+  const int tiles = p.mtiles / p.splits + (split < longer ? 1 : 0);  // >= 1: splits <= mtiles
   {
     const uint32_t tile_bytes = (uint32_t)Pipe::kAFrags * p.ks * 1024u;
     static_assert(Pipe::kBFrags == kWeightFrags, "tiles as laid out");
@@ -793,6 +801,10 @@ void launch_affinity_tiles(AffinityArgs p, const LaunchShape& l, hipStream_t s) 
   p.mtiles = l.mtiles;
   p.splits = l.splits;
   p.hsplits = l.hsplits;
+  // Where a CU gets several blocks the longer ones come first, and the others fill what these
+  // leave of the CUs: 4,000 tokens of an 8B-class layer 1,871 -> 1,683 us, of one of d = 2,048, I =
+  // 6,144 449 -> 343 us.  Otherwise one order for all, which shares more tiles in each L2.
+  p.first = (int64_t)p.I_pad / kBlockNeurons * l.splits * l.hsplits > device_cus() ? l.mtiles % l.splits : 0;
   const int rows = (p.G + l.hsplits - 1) / l.hsplits + 1;
   const size_t shm = sizeof(float) * 8 * rows * 32;
   const unsigned grid = (unsigned)(p.I_pad / kBlockNeurons * l.splits * l.hsplits);
