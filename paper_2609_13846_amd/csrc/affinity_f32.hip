@@ -115,11 +115,14 @@ fold_f32_kernel(float* __restrict__ wcat, const float* __restrict__ w_o, int N, 
 // 16-byte LDS reads per 8 instructions.  S = 32 reads each operand half as often from L2;
 // S = 16 gives four times the blocks and a quarter of the serial work per tile, for launches
 // that would leave CUs without a block.  Measured against one thread per (neuron, token
-// lane), whose lanes each walked a weight row of their own: 15,318 -> 184 us at d = 512,
-// I = 1536, 8 heads of 64, 2,048 tokens (70 TFLOP/s; a large fp32 product reaches 154), and
-// with S = 16 52 -> 11 us at d = 64, I = 128, 8 heads of 16, 512 tokens.
+// lane), whose lanes each walked a weight row of their own: 15,318 -> 139 us at d = 512,
+// I = 1536, 8 heads of 64, 2,048 tokens (93 TFLOP/s, matrix cores busy 62% at 2.25 GHz; a large
+// fp32 product reaches 154), and with S = 16 52 -> 12 us at d = 64, I = 128, 8 heads of 16, 512
+// tokens.  Of that, 180 -> 154 us are three wavefronts per SIMD, so that the 768 blocks run at
+// once, and the rest the loops over stages in which nothing but the products touches the
+// accumulators (epilogues inside a stage made the compiler copy all 32 in each).
 template <int S>
-__global__ void __launch_bounds__(kFThreads)
+__global__ void __launch_bounds__(kFThreads, 3)
 affinity_f32_kernel(AffinityF32Args p) {
   using M = MfmaF32<S>;
   constexpr int kRows = 2 * S;
@@ -165,36 +168,33 @@ affinity_f32_kernel(AffinityF32Args p) {
 #pragma unroll
       for (int j = 0; j < kBPer; ++j) bv[j] = *reinterpret_cast<const f32x4v*>(wp[j] + q * kFK);
     };
-    auto store = [&](int q) __attribute__((always_inline)) {
+    auto store = [&](int q, bool op) __attribute__((always_inline)) {
       const int buf = q & 1;
       if (stages_tokens) *reinterpret_cast<f32x4v*>(As[buf] + srow * kFRow + scol) = av;
 #pragma unroll
       for (int j = 0; j < kBPer; ++j)
         *reinterpret_cast<f32x4v*>(Bs[buf] + (srow + 64 * j) * kFRow + scol) = bv[j];
-      if (q < nq1) {
+      if (op) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) ss = fmaf(av[e], av[e], ss);
-        if (q == nq1 - 1) {  // the row's last columns: its four threads are neighbours
-          ss += __shfl_xor(ss, 1, 64);
-          ss += __shfl_xor(ss, 2, 64);
-          if (stages_tokens && scol == 0) rv[srow] = valid ? 1.0f / sqrtf(ss / (float)p.d + p.eps) : 0.0f;
-        }
       }
     };
     typename M::Acc acc[2] = {};
     float c1[M::kElems], c2[M::kElems];
     float colsum = 0.0f;
-    int head_stage = 0, h = 0;
     fetch(0);
-    store(0);
+    store(0, true);
     if (p.rinv_next && threadIdx.x < kRows) {
       const int64_t tn = (int64_t)mt * kRows + threadIdx.x;
       rv2[threadIdx.x] = tn < p.T ? p.rinv_next[tn] : 0.0f;
     }
     __syncthreads();
-    for (int q = 0; q < nq; ++q) {
+    // Products of stage q while q + 1 is on its way into the other buffer; nothing else in a
+    // stage touches the accumulators.
+    auto stage = [&](int q, bool op, bool last) __attribute__((always_inline)) {
       const int buf = q & 1;
-      if (q + 1 < nq) fetch(q + 1);
+      if (!last || q + 1 < nq) fetch(q + 1);
+      __builtin_amdgcn_sched_barrier(0);  // the loads first: they have the stage to land
 #pragma unroll
       for (int s = 0; s < kReads; ++s) {
         const int col = 4 * ((64 / S) * s + grp);
@@ -207,52 +207,56 @@ affinity_f32_kernel(AffinityF32Args p) {
           acc[1] = M::run(a[e], bu[e], acc[1]);
         }
       }
-      if (q == nq1 - 1) {
-        // Operating point: c1 = silu'(g) u / r, c2 = silu(g) / r (both 1/r for the ADD score).
-        float ds = 0.0f;
+      if (!last || q + 1 < nq) store(q + 1, op);
+      __syncthreads();
+    };
+    int q = 0;
+    for (; q < nq1 - 1; ++q) stage(q, true, false);
+    // The row's last columns are in: its four threads are neighbours.
+    ss += __shfl_xor(ss, 1, 64);
+    ss += __shfl_xor(ss, 2, 64);
+    if (stages_tokens && scol == 0) rv[srow] = valid ? 1.0f / sqrtf(ss / (float)p.d + p.eps) : 0.0f;
+    stage(q++, false, false);
+    // Operating point: c1 = silu'(g) u / r, c2 = silu(g) / r (both 1/r for the ADD score).
+    float ds = 0.0f;
 #pragma unroll
-        for (int i = 0; i < M::kElems; ++i) {
-          const int row = S * wm + M::row(i, lane);
-          const float ri = rv[row];
-          const float g = acc[0][i] * ri, u = acc[1][i] * ri;
-          const float sg = 1.0f / (1.0f + expf(-g));
-          if (p.rinv_next) {
-            const float a = g * sg * u * rv2[row];
-            ds = fmaf(a, a, ds);
-          }
-          c2[i] = p.add ? ri : g * sg * ri;
-          c1[i] = p.add ? ri : sg * (1.0f + g * (1.0f - sg)) * u * ri;
-        }
-        if (p.rinv_next) {
+    for (int i = 0; i < M::kElems; ++i) {
+      const int row = S * wm + M::row(i, lane);
+      const float ri = rv[row];
+      const float g = acc[0][i] * ri, u = acc[1][i] * ri;
+      const float sg = 1.0f / (1.0f + expf(-g));
+      if (p.rinv_next) {
+        const float a = g * sg * u * rv2[row];
+        ds = fmaf(a, a, ds);
+      }
+      c2[i] = p.add ? ri : g * sg * ri;
+      c1[i] = p.add ? ri : sg * (1.0f + g * (1.0f - sg)) * u * ri;
+    }
+    if (p.rinv_next) {
 #pragma unroll
-          for (int off = S; off < 64; off *= 2) ds += __shfl_xor(ds, off, 64);
-          if (lane < S) red[(wave * G1 + p.G) * S + lane] += ds;
-        }
-        acc[0] = typename M::Acc{};
-        acc[1] = typename M::Acc{};
-      } else if (q >= nq1 && ++head_stage == nqh) {
+      for (int off = S; off < 64; off *= 2) ds += __shfl_xor(ds, off, 64);
+      if (lane < S) red[(wave * G1 + p.G) * S + lane] += ds;
+    }
+    for (int h = 0; h < p.H;) {
+      acc[0] = typename M::Acc{};
+      acc[1] = typename M::Acc{};
+      for (int e = 0; e < nqh; ++e, ++q) stage(q, false, true);
 #pragma unroll
-        for (int i = 0; i < M::kElems; ++i) {
-          const float dg = c1[i] * acc[0][i], du = c2[i] * acc[1][i];
-          if (p.add) {
-            colsum = fmaf(dg, dg, fmaf(du, du, colsum));
-          } else {
-            const float dl = dg + du;
-            colsum = fmaf(dl, dl, colsum);
-          }
-        }
-        head_stage = 0;
-        acc[0] = typename M::Acc{};
-        acc[1] = typename M::Acc{};
-        if (++h % hpg == 0) {  // last query head of its KV group
-#pragma unroll
-          for (int off = S; off < 64; off *= 2) colsum += __shfl_xor(colsum, off, 64);
-          if (lane < S) red[(wave * G1 + h / hpg - 1) * S + lane] += colsum;
-          colsum = 0.0f;
+      for (int i = 0; i < M::kElems; ++i) {
+        const float dg = c1[i] * acc[0][i], du = c2[i] * acc[1][i];
+        if (p.add) {
+          colsum = fmaf(dg, dg, fmaf(du, du, colsum));
+        } else {
+          const float dl = dg + du;
+          colsum = fmaf(dl, dl, colsum);
         }
       }
-      if (q + 1 < nq) store(q + 1);
-      __syncthreads();
+      if (++h % hpg == 0) {  // last query head of its KV group
+#pragma unroll
+        for (int off = S; off < 64; off *= 2) colsum += __shfl_xor(colsum, off, 64);
+        if (lane < S) red[(wave * G1 + h / hpg - 1) * S + lane] += colsum;
+        colsum = 0.0f;
+      }
     }
   }
   __syncthreads();  // a split past the last tile ran none of the loop's barriers
