@@ -20,8 +20,7 @@
 //   transpose_fragments_kernel  W_o^T, fragment-major
 //   fold_kernel           F = W' W_o (MFMA)
 //   down_norm_*_kernel    n_d[k] = ||w^d_k||^2 (row chunks, then their fixed-order sum)
-//   rms_kernel            1/r per token
-//   tile_tokens_kernel    [x | a] rewritten fragment-major
+//   tile_tokens_kernel    1/r per token, [x | a] rewritten fragment-major
 //   affinity_bf16_kernel  the fused operating point + per-head damage + token reduction
 //   reduce_splits_kernel  deterministic fp64 sum of the per-split partials into A
 // Both operands of the fused kernel are fragment-major (frag_gemm.h).  The weights are one
@@ -217,37 +216,15 @@ down_norm_sum_kernel(const float* __restrict__ part, int chunks, int I, int I_pa
 }
 
 // ------------------------------------------------------------------ per-token scalars
-// rinv[t] = 1 / sqrt(mean_j x[t][j]^2 + eps), 0 for the padding rows T_tokens <= t < T_pad; one
-// wavefront per token.
-template <typename T>
+// rinv[t] = 1 / sqrt(mean_j x[t][j]^2 + eps) of fp32 rows; one wavefront per token.
 __global__ void __launch_bounds__(256)
-rms_kernel(const T* __restrict__ x, int64_t T_tokens, int64_t T_pad, int d, float eps,
-           float* __restrict__ rinv) {
+rms_kernel(const float* __restrict__ x, int64_t T, int d, float eps, float* __restrict__ rinv) {
   const int64_t t = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
-  if (t >= T_tokens) {  // whole wavefronts exit together
-    if (t < T_pad && lane == 0) rinv[t] = 0.0f;
-    return;
-  }
-  const T* row = x + t * d;
+  if (t >= T) return;  // whole wavefronts exit together
+  const float* row = x + t * d;
   float s = 0.0f;
-  if constexpr (sizeof(T) == 2) {
-    // d % 16 == 0: 16-byte loads of 8 bf16
-    for (int j = lane * 8; j < d; j += 64 * 8) {
-      const u32x4 v = *reinterpret_cast<const u32x4*>(row + j);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const float lo = __uint_as_float(v[e] << 16), hi = __uint_as_float(v[e] & 0xffff0000u);
-        s = fmaf(lo, lo, s);
-        s = fmaf(hi, hi, s);
-      }
-    }
-  } else {
-    for (int j = lane; j < d; j += 64) {
-      const float v = load_f32(row, j);
-      s = fmaf(v, v, s);
-    }
-  }
+  for (int j = lane; j < d; j += 64) s = fmaf(row[j], row[j], s);
   for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
   if (lane == 0) rinv[t] = 1.0f / sqrtf(s / (float)d + eps);
 }
@@ -261,6 +238,14 @@ rms_kernel(const T* __restrict__ x, int64_t T_tokens, int64_t T_pad, int d, floa
 // the token scale).  One thread moves one 16-byte piece; RUN consecutive threads read
 // 16 RUN contiguous bytes of a row.  Rows past the last token and the columns that round
 // d and dh up to whole stages (PAD) are zero.
+//
+// 1/r has no pass of its own: a block takes 16 tokens and a share of their columns, `per` units of
+// 8 RUN, and sums the squares of their x rows first (16 threads per row); with x_next the last
+// block of each 16 tokens takes 1/r' instead.  With one share per row x comes from HBM once, its
+// second reading from the L2; short slices take more shares, so that the blocks fill the chip, and
+// read x again in each.  Against a pass for 1/r and one for the tiles: 5,000 tokens of d = 1,040 and
+// 12 heads of 80 12.0 us instead of 8.7 + 4.9 and a launch; 32,768 tokens of d = 1,024, 16 heads of
+// 128 81 us instead of 65 + 14 (5.0 TB/s); a call of 1,000 of them, ADD, 42 -> 40 us.
 __device__ __forceinline__ float pow2_floor(float v) {  // 2^floor(log2 v), v normal and > 0
   return __uint_as_float(__float_as_uint(v) & 0x7f800000u);
 }
@@ -276,37 +261,77 @@ __device__ __forceinline__ uint32_t scale_bf16_pair(uint32_t w, float f) {
   return (__float_as_uint(lo) >> 16) | (__float_as_uint(hi) & 0xffff0000u);
 }
 
+struct TokenArgs {
+  const uint16_t *x, *attn, *x_next;  // x_next may be NULL
+  float eps, eps_next;
+  int T, T_pad, d, H, dh, dP, dhP;
+  uint16_t* xt;
+  float *rinv, *rinv_next;  // [T_pad], 0 past the last token
+};
+
 template <int F, int RUN, bool PAD>
 __global__ void __launch_bounds__(256)
-tile_tokens_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ attn,
-                   const float* __restrict__ rinv, int T, int d, int HD, int dh, int dP, int dhP,
-                   int units_per_row, uint32_t n_pieces, int ks, uint16_t* __restrict__ xt) {
-  const uint32_t g = blockIdx.x * 256 + threadIdx.x;
-  if (g >= n_pieces) return;
-  const uint32_t u = g / (16 * RUN), w = g % (16 * RUN);
-  const int t = 16 * (int)(u / units_per_row) + (int)(w / RUN);
-  const int k = 8 * (int)((u % units_per_row) * RUN + w % RUN);
-  u32x4 v = {0u, 0u, 0u, 0u};
-  if (t < T) {
-    if (k < dP) {
-      if (!PAD || k < d) v = *reinterpret_cast<const u32x4*>(x + (int64_t)t * d + k);
-    } else {
-      int col = k - dP;
-      bool real = true;
-      if constexpr (PAD) {
-        const int h = col / dhP, e = col % dhP;
-        real = e < dh;
-        col = h * dh + e;
-      }
-      if (real) {
-        v = *reinterpret_cast<const u32x4*>(attn + (int64_t)t * HD + col);
-        const float f = pow2_floor(rinv[t]);
+tile_tokens_kernel(TokenArgs p, int units, int per) {
+  __shared__ float rs[16];
+  const int t0 = 16 * blockIdx.x, HD = p.H * p.dh, ks = (p.dP + p.H * p.dhP) / kStage;
+  const int u0 = blockIdx.y * per, u1 = min(u0 + per, units);
+  const bool next = u0 >= units;
+  if (next || u0 == 0 || 8 * RUN * u1 > p.dP) {  // the head columns need 1/r
+    const int r = threadIdx.x / 16, t = t0 + r;
+    float lo = 0.0f, hi = 0.0f;
+    if (t < p.T) {
+      const uint16_t* row = (next ? p.x_next : p.x) + (int64_t)t * p.d;
+#pragma unroll 4
+      for (int j = 8 * (threadIdx.x % 16); j < p.d; j += 128) {  // d is a multiple of 16
+        const u32x4 v = *reinterpret_cast<const u32x4*>(row + j);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) v[j] = scale_bf16_pair(v[j], f);
+        for (int e = 0; e < 4; ++e) {
+          const float a = __uint_as_float(v[e] << 16), b = __uint_as_float(v[e] & 0xffff0000u);
+          lo = fmaf(a, a, lo);
+          hi = fmaf(b, b, hi);
+        }
       }
     }
+    float ss = lo + hi;
+#pragma unroll
+    for (int off = 8; off > 0; off /= 2) ss += __shfl_xor(ss, off, 64);
+    const float v = t < p.T ? 1.0f / sqrtf(ss / (float)p.d + (next ? p.eps_next : p.eps)) : 0.0f;
+    if (threadIdx.x % 16 == 0) {
+      rs[r] = v;
+      if (next)
+        p.rinv_next[t] = v;
+      else if (u0 == 0)
+        p.rinv[t] = v;
+    }
+    if (next) return;
+    __syncthreads();
   }
-  *reinterpret_cast<u32x4*>(xt + frag_offset<F>(t, k, ks)) = v;
+#pragma unroll 4
+  for (int i = threadIdx.x; i < (u1 - u0) * 16 * RUN; i += 256) {
+    const int w = i % (16 * RUN), t = t0 + w / RUN;
+    const int k = 8 * ((u0 + i / (16 * RUN)) * RUN + w % RUN);
+    u32x4 v = {0u, 0u, 0u, 0u};
+    if (t < p.T) {
+      if (k < p.dP) {
+        if (!PAD || k < p.d) v = *reinterpret_cast<const u32x4*>(p.x + (int64_t)t * p.d + k);
+      } else {
+        int col = k - p.dP;
+        bool real = true;
+        if constexpr (PAD) {
+          const int h = col / p.dhP, e = col % p.dhP;
+          real = e < p.dh;
+          col = h * p.dh + e;
+        }
+        if (real) {
+          v = *reinterpret_cast<const u32x4*>(p.attn + (int64_t)t * HD + col);
+          const float f = pow2_floor(rs[w / RUN]);
+#pragma unroll
+          for (int j = 0; j < 4; ++j) v[j] = scale_bf16_pair(v[j], f);
+        }
+      }
+    }
+    *reinterpret_cast<u32x4*>(p.xt + frag_offset<F>(t, k, ks)) = v;
+  }
 }
 
 // ------------------------------------------------------------------ fused affinity (bf16)
@@ -698,37 +723,6 @@ affinity_bf16_kernel(AffinityArgs p) {
   }
 }
 
-// Token rows rounded up to whole tiles.
-int64_t pad_tokens(int64_t T, int tile = kTokenPad) { return (T + tile - 1) / tile * tile; }
-
-template <int F>
-void launch_tile_tokens(const uint16_t* x, const uint16_t* attn, const float* rinv, int T, int T_pad, int d,
-                        int H, int dh, int dP, int dhP, uint16_t* xt, hipStream_t s) {
-  const int Kt = dP + H * dhP, HD = H * dh, ks = Kt / kStage;
-  const uint32_t n = (uint32_t)((int64_t)T_pad * Kt / 8);
-  const unsigned grid = (n + 255) / 256;
-  const bool pad = dP != d || dhP != dh;
-  if (Kt % 64 == 0 && !pad)
-    tile_tokens_kernel<F, 8, false><<<grid, 256, 0, s>>>(x, attn, rinv, T, d, HD, dh, dP, dhP, Kt / 64, n, ks, xt);
-  else if (!pad)
-    tile_tokens_kernel<F, 4, false><<<grid, 256, 0, s>>>(x, attn, rinv, T, d, HD, dh, dP, dhP, ks, n, ks, xt);
-  else
-    tile_tokens_kernel<F, 4, true><<<grid, 256, 0, s>>>(x, attn, rinv, T, d, HD, dh, dP, dhP, ks, n, ks, xt);
-}
-
-void launch_prep_gate_up(const uint16_t* w_gate, const uint16_t* w_up, const uint16_t* gamma, int I, int d,
-                         int dP, int I_pad, int ks, uint16_t* out, hipStream_t s) {
-  auto al16 = [](const void* p) { return ((uintptr_t)p & 15u) == 0; };
-  const uint32_t n = (uint32_t)((int64_t)2 * I_pad * dP / 8);
-  const unsigned grid = std::min<unsigned>((n + 255) / 256, 1u << 20);
-  if (!al16(w_gate) || !al16(w_up) || !al16(gamma))
-    prep_gate_up_fragments_kernel<4, false><<<grid, 256, 0, s>>>(w_gate, w_up, gamma, I, d, dP / 32, n, ks, out);
-  else if (dP % 64 == 0)
-    prep_gate_up_fragments_kernel<8, true><<<grid, 256, 0, s>>>(w_gate, w_up, gamma, I, d, dP / 64, n, ks, out);
-  else
-    prep_gate_up_fragments_kernel<4, true><<<grid, 256, 0, s>>>(w_gate, w_up, gamma, I, d, dP / 32, n, ks, out);
-}
-
 }  // namespace
 
 // Compute units of the current device, cached per device (atomics: calls on different
@@ -747,6 +741,38 @@ int device_cus() {
 }
 
 namespace {
+
+// Token rows rounded up to whole tiles.
+int64_t pad_tokens(int64_t T, int tile = kTokenPad) { return (T + tile - 1) / tile * tile; }
+
+template <int F>
+void launch_tile_tokens(const TokenArgs& p, hipStream_t s) {
+  const int Kt = p.dP + p.H * p.dhP, rows = p.T_pad / 16;
+  const bool pad = p.dP != p.d || p.dhP != p.dh, wide = Kt % 64 == 0 && !pad;
+  // Shares of a row's columns: two blocks per CU, of four units at least.
+  const int units = Kt / (wide ? 64 : 32), want = (2 * device_cus() + rows - 1) / rows;
+  const int per = std::max((units + want - 1) / want, std::min(units, 4));
+  const dim3 grid(rows, (units + per - 1) / per + (p.x_next ? 1 : 0));
+  if (wide)
+    tile_tokens_kernel<F, 8, false><<<grid, 256, 0, s>>>(p, units, per);
+  else if (!pad)
+    tile_tokens_kernel<F, 4, false><<<grid, 256, 0, s>>>(p, units, per);
+  else
+    tile_tokens_kernel<F, 4, true><<<grid, 256, 0, s>>>(p, units, per);
+}
+
+void launch_prep_gate_up(const uint16_t* w_gate, const uint16_t* w_up, const uint16_t* gamma, int I, int d,
+                         int dP, int I_pad, int ks, uint16_t* out, hipStream_t s) {
+  auto al16 = [](const void* p) { return ((uintptr_t)p & 15u) == 0; };
+  const uint32_t n = (uint32_t)((int64_t)2 * I_pad * dP / 8);
+  const unsigned grid = std::min<unsigned>((n + 255) / 256, 1u << 20);
+  if (!al16(w_gate) || !al16(w_up) || !al16(gamma))
+    prep_gate_up_fragments_kernel<4, false><<<grid, 256, 0, s>>>(w_gate, w_up, gamma, I, d, dP / 32, n, ks, out);
+  else if (dP % 64 == 0)
+    prep_gate_up_fragments_kernel<8, true><<<grid, 256, 0, s>>>(w_gate, w_up, gamma, I, d, dP / 64, n, ks, out);
+  else
+    prep_gate_up_fragments_kernel<4, true><<<grid, 256, 0, s>>>(w_gate, w_up, gamma, I, d, dP / 32, n, ks, out);
+}
 
 struct LaunchShape {
   int tile = kTokenPad;  // token rows per tile: 192, 128 or 64
@@ -1010,16 +1036,11 @@ dtp_status accumulate(dtp_layer L, const void* x, const void* attn, const void* 
       p.hpg = H / G;
       p.I_pad = L->I_pad;
       shape = choose_launch(p, add, T, L->tile_slice);
-      const int T_pad = shape.mtiles * shape.tile;
-      const unsigned rb = (unsigned)((T_pad + 3) / 4);
-      rms_kernel<uint16_t><<<rb, 256, 0, s>>>((const uint16_t*)xs, T, T_pad, dm, d.rms_eps, L->rinv);
-      if (xns)
-        rms_kernel<uint16_t><<<rb, 256, 0, s>>>((const uint16_t*)xns, T, T_pad, dm, eps_next, L->rinv_next);
-      (shape.tile == 64 ? launch_tile_tokens<4> : shape.tile == 128 ? launch_tile_tokens<8> : launch_tile_tokens<12>)(
-          (const uint16_t*)xs, (const uint16_t*)as, L->rinv, T, T_pad, dm, H, dh, L->dP, L->dhP, L->xt, s);
+      TokenArgs t{(const uint16_t*)xs, (const uint16_t*)as, (const uint16_t*)xns, d.rms_eps, eps_next, T,
+                  shape.mtiles * shape.tile, dm, H, dh, L->dP, L->dhP, L->xt, L->rinv, L->rinv_next};
+      (shape.tile == 64 ? launch_tile_tokens<4> : shape.tile == 128 ? launch_tile_tokens<8> : launch_tile_tokens<12>)(t, s);
     } else if (xns) {  // the fp32 kernel takes 1/r from the rows that it stages
-      rms_kernel<float><<<(unsigned)((T + 3) / 4), 256, 0, s>>>((const float*)xns, T, T, dm, eps_next,
-                                                                L->rinv_next);
+      rms_kernel<<<(unsigned)((T + 3) / 4), 256, 0, s>>>((const float*)xns, T, dm, eps_next, L->rinv_next);
     }
     DTP_HIP(hipGetLastError());
 
