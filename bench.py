@@ -32,7 +32,7 @@ sys.path.insert(0, ROOT)
 
 PEAK_BF16_TFLOPS = 2516.6   # MI355X dense bf16 MFMA
 METRIC = "affinity calibration tokens/s per layer + % bf16 MFMA peak; full-model layout time"
-KERNEL_SRC = os.path.join(ROOT, "paper_2609_13846_amd", "csrc", "affinity.hip")
+KERNEL_SRC = [os.path.join(ROOT, "paper_2609_13846_amd", "csrc", f) for f in ("affinity.hip", "frag_gemm.h")]
 PROFILES = os.path.join(ROOT, "profiles")
 
 
@@ -46,7 +46,7 @@ def flops_per_token(wl) -> float:
 
 
 def kernel_hash() -> str:
-    return hashlib.sha256(open(KERNEL_SRC, "rb").read()).hexdigest()[:16]
+    return hashlib.sha256(b"".join(open(f, "rb").read() for f in KERNEL_SRC)).hexdigest()[:16]
 
 
 def traffic_record(wl):

@@ -263,7 +263,7 @@ typedef struct {
 
 /* Coordinate ascent over a chain of N layers (Section 3, "Optimiser"): start from the
  * contiguous head assignment h_i(g) = g/(G/L); each sweep runs the neuron step of every
- * layer (host) and then the head step of every layer (GPU partition scores); stop at the
+ * layer and then the head step of every layer (GPU partition scores); stop at the
  * first sweep whose J_int is not strictly better than the previous sweep's, or after
  * max_sweeps.  Each matrix is encoded to unit mass separately.
  *   A_up   dev [N, G, I] float  raw up affinity of each layer (from dtp_affinity_accumulate)
