@@ -36,6 +36,7 @@
 
 #include "dtp_internal.h"
 #include "frag_gemm.h"
+#include "prep_index.h"
 #include "tile_mfma.h"
 
 namespace dtp {
@@ -80,17 +81,17 @@ __global__ void prep_gate_up_kernel(const float* __restrict__ w_gate, const floa
 
 // The same for the bf16 path: row R of the fragment-major weights is the gate (R % 64 < 32) or
 // up row of neuron 32 (R / 64) + R % 32; columns j < dP, zero past d and for padding neurons.
-// One thread per 16-byte piece (d is a multiple of 16), 16 rows x RUN pieces per unit so that
-// RUN consecutive threads read 16 RUN contiguous bytes.  VEC: 16-byte aligned inputs.
+// One thread per 16-byte piece (d is a multiple of 16), placed by prep_place and counted in 64
+// bits.  VEC: 16-byte aligned inputs.
 template <int RUN, bool VEC>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(kPrepThreads)
 prep_gate_up_fragments_kernel(const uint16_t* __restrict__ w_gate, const uint16_t* __restrict__ w_up,
                               const uint16_t* __restrict__ gamma, int I, int d, int units_per_row,
-                              uint32_t n_pieces, int ks, uint16_t* __restrict__ out) {
-  for (uint32_t g = blockIdx.x * 256 + threadIdx.x; g < n_pieces; g += gridDim.x * 256) {
-    const uint32_t u = g / (16 * RUN), w = g % (16 * RUN);
-    const uint32_t row = 16 * (u / units_per_row) + w / RUN;
-    const int j = 8 * (int)((u % units_per_row) * RUN + w % RUN);
+                              uint64_t n_pieces, int ks, uint16_t* __restrict__ out) {
+  for (uint64_t g = prep_first(blockIdx.x, threadIdx.x); g < n_pieces; g = prep_next(g, gridDim.x)) {
+    const PrepPlace at = prep_place<RUN>(g, units_per_row);
+    const uint32_t row = at.row;
+    const int j = at.col;
     const int k = (int)(row / 64) * 32 + (int)(row % 32);
     u32x4 o = {0u, 0u, 0u, 0u};
     if (k < I && j < d) {
@@ -764,14 +765,12 @@ void launch_tile_tokens(const TokenArgs& p, hipStream_t s) {
 void launch_prep_gate_up(const uint16_t* w_gate, const uint16_t* w_up, const uint16_t* gamma, int I, int d,
                          int dP, int I_pad, int ks, uint16_t* out, hipStream_t s) {
   auto al16 = [](const void* p) { return ((uintptr_t)p & 15u) == 0; };
-  const uint32_t n = (uint32_t)((int64_t)2 * I_pad * dP / 8);
-  const unsigned grid = std::min<unsigned>((n + 255) / 256, 1u << 20);
-  if (!al16(w_gate) || !al16(w_up) || !al16(gamma))
-    prep_gate_up_fragments_kernel<4, false><<<grid, 256, 0, s>>>(w_gate, w_up, gamma, I, d, dP / 32, n, ks, out);
-  else if (dP % 64 == 0)
-    prep_gate_up_fragments_kernel<8, true><<<grid, 256, 0, s>>>(w_gate, w_up, gamma, I, d, dP / 64, n, ks, out);
+  const uint64_t n = prep_pieces(I_pad, dP);
+  const unsigned grid = prep_blocks(n);
+  if (al16(w_gate) && al16(w_up) && al16(gamma))  // dP is a multiple of 128
+    prep_gate_up_fragments_kernel<8, true><<<grid, kPrepThreads, 0, s>>>(w_gate, w_up, gamma, I, d, dP / 64, n, ks, out);
   else
-    prep_gate_up_fragments_kernel<4, true><<<grid, 256, 0, s>>>(w_gate, w_up, gamma, I, d, dP / 32, n, ks, out);
+    prep_gate_up_fragments_kernel<4, false><<<grid, kPrepThreads, 0, s>>>(w_gate, w_up, gamma, I, d, dP / 32, n, ks, out);
 }
 
 struct LaunchShape {
