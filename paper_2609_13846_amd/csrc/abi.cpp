@@ -540,6 +540,7 @@ dtp_status dtp_coordinate_ascent(int32_t N, int32_t G, int32_t I, int32_t L, con
     ws.value = (int64_t*)(dev + value_at);
     ws.h = (int32_t*)(dev + h_at);
     ws.moves = (const uint8_t*)(dev + moves_at);
+    ws.frozen = std::all_of(moves, moves + N, [](uint8_t m) { return m == 0; });
     const bool minimise = opt.minimise != 0;
     int32_t* const nu_dev = (int32_t*)(dev + nu_at);
     const int minim = minimise ? 1 : 0;

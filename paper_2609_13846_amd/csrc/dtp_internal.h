@@ -136,6 +136,8 @@ struct ScoreWorkspace {
   const uint8_t* moves = nullptr;  // dev [N]
   int32_t* h = nullptr;            // dev [N][G]
   int64_t* value = nullptr;        // dev [N]
+  // No layer's heads move: the values are those of h as it is, and nothing is scored.
+  bool frozen = false;
   // The gain matrices of the neuron step, M[i][k][l] = sum_{g: h_i(g)=l} Q_up[i][g][k] +
   // sum_{g: h_{i+1}(g)=l} Q_down[i][k][g], negated with `minimise`; M dev [N][I][L], from this
   // workspace's h.  Set by score_workspace_create.
