@@ -7,12 +7,10 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
-#include <exception>
 #include <mutex>
-#include <system_error>
-#include <thread>
 
 #include "dtp_internal.h"
+#include "host_threads.h"
 
 namespace dtp {
 
@@ -199,42 +197,7 @@ PinnedPool& pinned_pool() {
   return *pool;
 }
 
-constexpr int kMaxSolverThreads = 16;
 constexpr size_t kEagerGainBytes = size_t(256) << 10;
-
-// Threads of a sweep's neuron step: one per 200 us of it, about what starting and joining one
-// costs several times over.  (An exact solution takes about 10 ns per neuron with two devices,
-// 15 per neuron and device with more.)
-int solver_threads(int N, int I, int L) {
-  const int64_t ns = (int64_t)N * I * (L == 2 ? 10 : 15 * L);
-  const int hw = (int)std::max(1u, std::thread::hardware_concurrency());
-  return (int)std::max<int64_t>(1, std::min<int64_t>({ns / 200000, kMaxSolverThreads, hw}));
-}
-
-// Runs `work` on n threads, this one among them.  A thread that cannot be started is done
-// without (the others take its share); what any of them throws is thrown here.
-template <typename F>
-void run_on_threads(int n, F&& work) {
-  std::mutex mu;
-  std::exception_ptr failed;
-  auto guarded_work = [&]() {
-    try {
-      work();
-    } catch (...) {
-      std::lock_guard<std::mutex> lock(mu);
-      failed = std::current_exception();
-    }
-  };
-  std::vector<std::thread> pool;
-  pool.reserve((size_t)n);
-  try {
-    for (int t = 1; t < n; ++t) pool.emplace_back(guarded_work);
-  } catch (const std::system_error&) {
-  }
-  guarded_work();
-  for (auto& th : pool) th.join();
-  if (failed) std::rethrow_exception(failed);
-}
 
 // A pinned block for one call, or (if pinned memory cannot be had) pageable memory.
 struct HostStaging {
@@ -563,6 +526,9 @@ dtp_status dtp_coordinate_ascent(int32_t N, int32_t G, int32_t I, int32_t L, con
       }
       return DTP_OK;
     };
+    // The exact solver takes about 15 ns per neuron and device, the dual ascent at least 200 us.
+    const int64_t solver_ns = opt.dual_ascent_neurons ? std::max<int64_t>(200000, (int64_t)I * L * 250)
+                                                      : (int64_t)I * L * 15;
     int64_t J_prev = 0;
     int sweep = 0;
     DTP_HIP(hipMemcpyAsync(dev + nu_at, host.base + nu_at, q_at - nu_at, hipMemcpyHostToDevice, s));
@@ -611,7 +577,7 @@ dtp_status dtp_coordinate_ascent(int32_t N, int32_t G, int32_t I, int32_t L, con
                 balanced_assign_exact(I, L, Mi, nu_i, nullptr);
             }
           };
-          run_on_threads(std::min(N, opt.dual_ascent_neurons ? kMaxSolverThreads : solver_threads(N, I, L)), work);
+          run_on_threads(threads_for(N, solver_ns), work);
         }
         // Head block, then (the heads on the device already moved) the next sweep's gains: always
         // after the first sweep, which another follows, and later where the copy costs no more
@@ -724,13 +690,11 @@ dtp_status dtp_layer_optimum(int32_t G, int32_t I, int32_t L, const int64_t* Q_u
       neuron_gain(G, I, L, Q_up, hh, nullptr, nullptr, false, &M);
       balanced_assign_exact(I, L, M.data(), nus[j].data(), &value[j]);
     };
-    const unsigned hw = std::max(1u, std::min(16u, std::thread::hardware_concurrency()));
-    std::vector<std::thread> pool;
-    for (unsigned t = 0; t < hw; ++t)
-      pool.emplace_back([&, t] {
-        for (size_t j = t; j < reps.size(); j += hw) solve(j);
-      });
-    for (auto& th : pool) th.join();
+    std::atomic<size_t> next{0};
+    const int hw = (int)std::max(1u, std::min(16u, std::thread::hardware_concurrency()));
+    run_on_threads(hw, [&]() {
+      for (size_t j = next++; j < reps.size(); j = next++) solve(j);
+    });
     size_t best = 0;  // first partition (lexicographic) attaining the maximum
     for (size_t j = 1; j < reps.size(); ++j)
       if (value[j] > value[best]) best = j;
