@@ -28,6 +28,9 @@
  *     state (their scratch comes per call from the stream-ordered allocator).  Calls on
  *     one dtp_layer share its workspace and must be ordered by the caller (one stream,
  *     or synchronised); so must overlapping calls of dtp_down_weights_noalloc on a device.
+ *   - That scratch stays in the device's default memory pool, whose release threshold the
+ *     library raises to 1 GiB on its first use (and never lowers); what a call needs beyond
+ *     the threshold goes back to the device and is paid for again by the next such call.
  *   - Weights use the PyTorch nn.Linear layout [out_features, in_features].
  *   - bf16 tensors are IEEE bfloat16 bit patterns (uint16); f32 tensors are float.
  */

@@ -228,8 +228,10 @@ hipError_t stream_alloc(void** p, size_t bytes, hipStream_t s) {
     if (!retained[dev]) {
       hipMemPool_t pool;
       if (hipDeviceGetDefaultMemPool(&pool, dev) == hipSuccess) {
-        uint64_t keep = (uint64_t)1 << 30;
-        (void)hipMemPoolSetAttribute(pool, hipMemPoolAttrReleaseThreshold, &keep);
+        // Raised, never lowered: the pool is also the program's.
+        uint64_t keep = 0, own = (uint64_t)1 << 30;
+        if (hipMemPoolGetAttribute(pool, hipMemPoolAttrReleaseThreshold, &keep) != hipSuccess || keep < own)
+          (void)hipMemPoolSetAttribute(pool, hipMemPoolAttrReleaseThreshold, &own);
       }
       retained[dev] = true;
     }

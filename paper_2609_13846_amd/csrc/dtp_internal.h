@@ -60,7 +60,7 @@ constexpr int kFracBits = 48;
 constexpr int kMantBits = 40;
 
 // ---- stream-ordered scratch (abi.cpp): hipMallocAsync / hipFreeAsync from the device's
-// default pool, which is told once per device to keep up to 1 GiB of freed memory (what
+// default pool, which is told once per device to keep at least 1 GiB of freed memory (what
 // goes beyond it goes back to the device at the next synchronisation), so per-call scratch
 // costs neither a device-wide synchronisation nor a trip to the driver.
 hipError_t stream_alloc(void** p, size_t bytes, hipStream_t s);
