@@ -16,7 +16,8 @@
 //   down_weight_frag_kernel  one block per (256 neurons, 256 or 128 rows of W^{qkv}_g, group):
 //                            MFMA over d, then per-column sums of squares of each 128 rows
 //   down_weight_bf16_kernel  the same straight from the caller's matrices, for the
-//                            allocation-free call: 128 neurons x 128 rows per block
+//                            allocation-free call and where the copies' launches would
+//                            be too large: 128 neurons x 128 rows per block
 //   down_weight_f32_kernel   the same with plain FMAs, one thread per (group, neuron)
 //   down_rows_reduce_kernel  B[g, k] = fixed-order fp64 sum over the row chunks
 //   down_combine_kernel      S_down[k, g] = s[k] B[g, k]
@@ -289,6 +290,16 @@ dtp_status noalloc_scratch(float** out) {
   return DTP_OK;
 }
 
+// Whether the operands are copied fragment-major first: while the launches over the copies hold
+// fewer than 2^32 threads each.  (Thousands of groups of a few rows, each padded to a chunk,
+// do not: 4,096 at d = 65,536.)  The kernel of the allocation-free call, whose grid has the groups
+// in a dimension of their own, takes those with the same bits; where both can run it is the
+// slower one, 435 us against 102 for 128 groups of 24 rows at d = 1,024, I = 3,072.
+bool copies_launch(int64_t rows, int64_t n_frags, int64_t col_tiles) {
+  constexpr int64_t kThreads = (int64_t)1 << 32;
+  return n_frags * 64 < kThreads && rows / kDRows * col_tiles * 512 < kThreads;
+}
+
 // Shared body of dtp_down_weights and dtp_down_weights_noalloc.  The scratch of the row-chunk
 // sums comes from the stream-ordered allocator, or with `use_static` from the current
 // device's copy of `scratch` (the call is refused when it would not fit).
@@ -342,11 +353,25 @@ dtp_status down_weights(int32_t d_model, int32_t n_neurons, int32_t n_q_heads, i
   DTP_CHECK(d_model % 8 == 0, DTP_ERR_INVALID_ARG, "d_model=%d is not a multiple of 8", d_model);
   DTP_CHECK(n_neurons % 8 == 0, DTP_ERR_INVALID_ARG, "n_neurons=%d is not a multiple of 8",
             n_neurons);
+  // Scratch of the copying form in one block: [partial sums | neuron fragments | row fragments].
+  const int ks = (d_model + 31) / 32;
+  const int col_tiles = (n_neurons + 255) / 256;
+  const int64_t rows = (int64_t)n_kv_groups * n_chunks * kDRows;
+  const int64_t n_frags = rows / 16 * ks;
+  const size_t part_bytes = (sizeof(float) * (size_t)GI * n_chunks + 1023) / 1024 * 1024;
+  const size_t tw_bytes = (size_t)col_tiles * 256 * ks * 64, qkv_bytes = (size_t)rows * ks * 64;
   float* partial = nullptr;
+  char* base = nullptr;
   hipError_t e = hipSuccess;
   if (use_static) {
     dtp_status st = noalloc_scratch(&partial);
     if (st != DTP_OK) return st;
+  } else {
+    const bool copy = copies_launch(rows, n_frags, col_tiles);
+    DTP_HIP(stream_alloc((void**)&partial, part_bytes + (copy ? tw_bytes + qkv_bytes : 0), s));
+    if (copy) base = (char*)partial;
+  }
+  if (base == nullptr) {
     const dim3 grid((n_neurons + kDCols - 1) / kDCols, n_chunks, n_kv_groups);
     down_weight_bf16_kernel<<<grid, kDThreads, 0, s>>>(
         (const uint16_t*)w_q, (const uint16_t*)w_k, (const uint16_t*)w_v,
@@ -354,21 +379,11 @@ dtp_status down_weights(int32_t d_model, int32_t n_neurons, int32_t n_q_heads, i
         partial);
     e = hipGetLastError();
   } else {
-    // One block of scratch: [partial sums | neuron fragments | row fragments].
-    const int ks = (d_model + 31) / 32;
-    const int col_tiles = (n_neurons + 255) / 256;
-    const int64_t rows = (int64_t)n_kv_groups * n_chunks * kDRows;
-    const size_t part_bytes = (sizeof(float) * (size_t)GI * n_chunks + 1023) / 1024 * 1024;
-    const size_t tw_bytes = (size_t)col_tiles * 256 * ks * 64, qkv_bytes = (size_t)rows * ks * 64;
-    char* base = nullptr;
-    DTP_HIP(stream_alloc((void**)&base, part_bytes + tw_bytes + qkv_bytes, s));
-    partial = (float*)base;
     uint16_t* tw = (uint16_t*)(base + part_bytes);
     uint16_t* qkv = (uint16_t*)(base + part_bytes + tw_bytes);
     const dim3 tg(col_tiles * 4, (ks + 1) / 2);
     transpose_fragments_kernel<16, true, true><<<tg, 256, 0, s>>>((const uint16_t*)w_down, (const uint16_t*)gamma_next,
                                                    d_model, n_neurons, ks, tw);
-    const int64_t n_frags = rows / 16 * ks;
     // Two chunks per block where a group has an even number of them: half the neuron
     // fragments read per product.
     auto launch = [&](auto af) {
