@@ -126,7 +126,8 @@ down_weight_frag_kernel(const uint16_t* __restrict__ qkv, const uint16_t* __rest
 
 // partial[g][chunk][k] = sum over the chunk's rows rho of (W^{qkv}_g[rho] . (gamma' * w^d_k))^2.
 // The allocation-free form: each stage scales and transposes its slice of W_down itself, for
-// want of room for a copy.
+// want of room for a copy.  Bound by that transposition's LDS writes: as words of two rows
+// 265 us, as halves 431, for 128 groups of 24 rows at d = 1,024, I = 3,072.
 __global__ void __launch_bounds__(kDThreads)
 down_weight_bf16_kernel(const uint16_t* __restrict__ w_q, const uint16_t* __restrict__ w_k,
                         const uint16_t* __restrict__ w_v, const uint16_t* __restrict__ gamma,
@@ -158,9 +159,7 @@ down_weight_bf16_kernel(const uint16_t* __restrict__ w_q, const uint16_t* __rest
 #pragma unroll
     for (int pass = 0; pass < 2; ++pass) {
       bv[pass] = u32x4{0u, 0u, 0u, 0u};
-      const int idx = threadIdx.x + kDThreads * pass;
-      const int jj = idx / 16, kseg = idx % 16;
-      const int j = kc + jj, k = k0 + 8 * kseg;
+      const int j = kc + 2 * (threadIdx.x / 16) + pass, k = k0 + 8 * (threadIdx.x % 16);
       // I % 8 == 0: the 8 neurons are all valid or all past I
       if (j < d && k < I) bv[pass] = *reinterpret_cast<const u32x4*>(w_down + (int64_t)j * I + k);
       bg[pass] = j < d ? bf16_to_f32(gamma[j]) : 0.0f;
@@ -172,16 +171,15 @@ down_weight_bf16_kernel(const uint16_t* __restrict__ w_q, const uint16_t* __rest
       const int row = threadIdx.x / 4 + 64 * pass, seg = threadIdx.x % 4;
       *reinterpret_cast<u32x4*>(As[buf] + row * kDRow + 8 * seg) = av[pass];
     }
+    // scaled by gamma'[j] and stored transposed, [k][j], the two rows of a thread as one word
 #pragma unroll
-    for (int pass = 0; pass < 2; ++pass) {
-      // scaled by gamma'[j] and stored transposed, [k][j]
-      const int idx = threadIdx.x + kDThreads * pass;
-      const int jj = idx / 16, kseg = idx % 16;
+    for (int e = 0; e < 8; ++e) {
+      uint16_t w[2];
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const uint16_t w = (uint16_t)(bv[pass][e / 2] >> (16 * (e % 2)));
-        Bs[buf][(8 * kseg + e) * kDRow + jj] = f32_to_bf16(bf16_to_f32(w) * bg[pass]);
-      }
+      for (int pass = 0; pass < 2; ++pass)
+        w[pass] = f32_to_bf16(bf16_to_f32((uint16_t)(bv[pass][e / 2] >> (16 * (e % 2)))) * bg[pass]);
+      *reinterpret_cast<uint32_t*>(Bs[buf] + (8 * (threadIdx.x % 16) + e) * kDRow + 2 * (threadIdx.x / 16)) =
+          (uint32_t)w[0] | ((uint32_t)w[1] << 16);
     }
   };
   fetch(0);
@@ -294,7 +292,7 @@ dtp_status noalloc_scratch(float** out) {
 // fewer than 2^32 threads each.  (Thousands of groups of a few rows, each padded to a chunk,
 // do not: 4,096 at d = 65,536.)  The kernel of the allocation-free call, whose grid has the groups
 // in a dimension of their own, takes those with the same bits; where both can run it is the
-// slower one, 435 us against 102 for 128 groups of 24 rows at d = 1,024, I = 3,072.
+// slower one, 265 us against 104 for 128 groups of 24 rows at d = 1,024, I = 3,072.
 bool copies_launch(int64_t rows, int64_t n_frags, int64_t col_tiles) {
   constexpr int64_t kThreads = (int64_t)1 << 32;
   return n_frags * 64 < kThreads && rows / kDRows * col_tiles * 512 < kThreads;
