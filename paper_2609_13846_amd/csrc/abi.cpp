@@ -198,6 +198,11 @@ PinnedPool& pinned_pool() {
 }
 
 constexpr size_t kEagerGainBytes = size_t(256) << 10;
+// Codes of an ascent that come to the host whole, where the gain matrices are then summed (1 ns
+// per code): summing them on the device is a launch and a wait more.  One layer of 4 groups and
+// 256 neurons, L = 4: 136 us an ascent, and 175 with the device's sums; of 12 groups and 384
+// neurons, 36 KB, L = 3: 593 and 613.
+constexpr size_t kHostGainBytes = size_t(48) << 10;
 
 // A pinned block for one call, or (if pinned memory cannot be had) pageable memory.
 struct HostStaging {
@@ -446,40 +451,50 @@ dtp_status dtp_coordinate_ascent(int32_t N, int32_t G, int32_t I, int32_t L, con
 
     // The codes stay on the device.  With two devices the neuron step runs there too, and only
     // the head step's values (each layer's part of J) come back after a sweep; otherwise it
-    // runs on the host, from the gain matrices (M).  Device scratch, in this order, so that
-    // what is copied together is contiguous:
-    // [encode stats | M | value | nu | h | best | moves | neuron moves | Q_up | Q_down].
+    // runs on the host, from the gain matrices (M), or from the codes where they are few.
+    // Device scratch, in this order, so that what is copied together is contiguous:
+    // [Q_up | Q_down | keys | encode stats | M | value | h | nu | best | moves | neuron moves].
     const int nmat = N + (has_down ? N - 1 : 0);
     const bool neurons = !opt.freeze_neurons;
     const bool on_device = neurons && L == 2 && !opt.dual_ascent_neurons;
     const bool on_host = neurons && !on_device;
     auto up = [](size_t b) { return (b + 255) & ~size_t(255); };
-    const size_t st_bytes = up(sizeof(EncodeStats) * nmat);
-    // M, or the keys of the selection on the device
-    const size_t m_bytes = neurons ? up(sizeof(int64_t) * (size_t)N * I * (on_device ? 1 : L)) : 0;
+    const size_t q_bytes = up(sizeof(int64_t) * (nup + ndown)), st_bytes = up(sizeof(EncodeStats) * nmat);
+    const bool host_gains = on_host && q_bytes <= kHostGainBytes;
+    const size_t keys_bytes = on_device ? up(sizeof(int64_t) * (size_t)N * I) : 0;  // of the selection there
+    const size_t m_bytes = on_host && !host_gains ? up(sizeof(int64_t) * (size_t)N * I * L) : 0;
     const size_t value_bytes = up(sizeof(int64_t) * (size_t)N);
     const size_t nu_bytes = up(sizeof(int32_t) * (size_t)N * I), h_bytes = up(sizeof(int32_t) * (size_t)N * G);
-    const size_t m_at = st_bytes, value_at = m_at + m_bytes, nu_at = value_at + 2 * value_bytes;
-    const size_t h_at = nu_at + nu_bytes, best_at = h_at + h_bytes, moves_at = best_at + value_bytes;
-    const size_t flags_at = moves_at + up((size_t)N), q_at = flags_at + up((size_t)N);
+    const size_t st_at = q_bytes + keys_bytes, m_at = st_at + st_bytes, value_at = m_at + m_bytes;
+    const size_t h_at = value_at + 2 * value_bytes, nu_at = h_at + h_bytes, best_at = nu_at + nu_bytes;
+    const size_t moves_at = best_at + value_bytes, flags_at = moves_at + up((size_t)N);
+    const size_t end_at = flags_at + up((size_t)N);
     DevBuf block(s);
-    DTP_HIP(stream_alloc(&block.p, q_at + sizeof(int64_t) * (nup + ndown), s));
+    DTP_HIP(stream_alloc(&block.p, end_at, s));
     char* const dev = (char*)block.p;
-    int64_t* const qu_dev = (int64_t*)(dev + q_at);
+    int64_t* const qu_dev = (int64_t*)dev;
     int64_t* const qd_dev = has_down ? qu_dev + nup : nullptr;
     int64_t* const m_dev = (int64_t*)(dev + m_at);
     st = launch_encode_unit_mass(A_up, N, A_down, has_down ? N - 1 : 0, (int64_t)G * I, qu_dev,
-                                 qd_dev, (EncodeStats*)dev, s);
+                                 qd_dev, (EncodeStats*)(dev + st_at), s);
     if (st != DTP_OK) return st;
-    // The host mirror of all but the codes, in pinned memory.
-    HostStaging host(q_at);
-    const EncodeStats* stats = (const EncodeStats*)host.base;
-    const int64_t* M = (const int64_t*)(host.base + m_at);
-    const int64_t* value = (const int64_t*)(host.base + value_at);  // of two sweeps
-    int32_t* const nus = (int32_t*)(host.base + nu_at);
-    int32_t* const hs = (int32_t*)(host.base + h_at);
-    uint8_t* const moves = (uint8_t*)(host.base + moves_at);
-    uint8_t* const flags = (uint8_t*)(host.base + flags_at);
+    // The host mirror, in pinned memory: of the codes only where they are few.
+    const size_t mirror_at = host_gains ? 0 : st_at;
+    HostStaging host(end_at - mirror_at);
+    auto mirror = [&](size_t at) { return host.base + (at - mirror_at); };
+    auto fetch = [&](size_t from, size_t to) {
+      return hipMemcpyAsync(mirror(from), dev + from, to - from, hipMemcpyDeviceToHost, s);
+    };
+    auto send = [&](size_t from, size_t to) {
+      return hipMemcpyAsync(dev + from, mirror(from), to - from, hipMemcpyHostToDevice, s);
+    };
+    const EncodeStats* stats = (const EncodeStats*)mirror(st_at);
+    const int64_t* M = (const int64_t*)mirror(m_at);
+    const int64_t* value = (const int64_t*)mirror(value_at);  // of two sweeps
+    int32_t* const nus = (int32_t*)mirror(nu_at);
+    int32_t* const hs = (int32_t*)mirror(h_at);
+    uint8_t* const moves = (uint8_t*)mirror(moves_at);
+    uint8_t* const flags = (uint8_t*)mirror(flags_at);
     // Contiguous start.
     auto layer_moves = [&](int i) { return opt.layer_mask == nullptr || opt.layer_mask[i] != 0; };
     for (int i = 0; i < N; ++i) {
@@ -511,7 +526,7 @@ dtp_status dtp_coordinate_ascent(int32_t N, int32_t G, int32_t I, int32_t L, con
     const int minim = minimise ? 1 : 0;
     auto neuron_block = [&]() {
       return ws.two_device_neurons(ws, qu_dev, qd_dev, minim, (const uint8_t*)(dev + flags_at),
-                                   (uint64_t*)m_dev, nu_dev, s);
+                                   (uint64_t*)(dev + q_bytes), nu_dev, s);
     };
     auto head_block = [&]() { return launch_partition_scores(ws, qu_dev, nu_dev, qd_dev, nu_dev, minim, s); };
     auto gains = [&]() { return ws.neuron_gains(ws, qu_dev, qd_dev, minim, m_dev, s); };
@@ -533,33 +548,34 @@ dtp_status dtp_coordinate_ascent(int32_t N, int32_t G, int32_t I, int32_t L, con
                                                       : (int64_t)I * L * 15;
     int64_t J_prev = 0;
     int sweep = 0;
-    DTP_HIP(hipMemcpyAsync(dev + nu_at, host.base + nu_at, q_at - nu_at, hipMemcpyHostToDevice, s));
+    if (!host_gains) DTP_HIP(send(h_at, end_at));
     if (!on_host) {
       // Every sweep on the device.  The first is followed by a second, so the two are queued
       // together; J of each comes back with the layout that the last one left.  (Codes of a
       // matrix that could not be encoded are whatever the scratch held: their sweeps end like
-      // any other, and the outcome is dropped.)
+      // any other, and the outcome is dropped.)  Where nothing moves the second has the first's J.
+      const bool still = ws.frozen && !neurons;
       for (bool done = false; !done;) {
         const int first = sweep, queued = sweep == 0 ? std::min(2, opt.max_sweeps) : 1;
         for (int j = 0; j < queued; ++j, ++sweep) {
+          if (still && sweep > 0) continue;
           ws.value = (int64_t*)(dev + value_at + j * value_bytes);
           if (neurons && (st = neuron_block()) != DTP_OK) return st;
           if ((st = head_block()) != DTP_OK) return st;
         }
-        if (first == 0) DTP_HIP(hipMemcpyAsync(host.base, dev, st_bytes, hipMemcpyDeviceToHost, s));
-        DTP_HIP(hipMemcpyAsync(host.base + value_at, dev + value_at, best_at - value_at, hipMemcpyDeviceToHost, s));
+        DTP_HIP(fetch(first == 0 ? st_at : value_at, best_at));
         DTP_HIP(hipStreamSynchronize(s));
         if (first == 0 && (st = check_stats()) != DTP_OK) return st;
         for (int j = 0; j < queued; ++j) {
-          const int64_t Jc = total((const int64_t*)((const char*)value + j * value_bytes));
+          const int64_t Jc = total((const int64_t*)((const char*)value + (still ? 0 : j) * value_bytes));
           done = first + j + 1 >= opt.max_sweeps ||
                  (first + j > 0 && !(minimise ? Jc < J_prev : Jc > J_prev));
           J_prev = Jc;
         }
       }
     } else {
-      if ((st = gains()) != DTP_OK) return st;
-      DTP_HIP(hipMemcpyAsync(host.base, dev, st_bytes + m_bytes, hipMemcpyDeviceToHost, s));
+      if (!host_gains && (st = gains()) != DTP_OK) return st;
+      DTP_HIP(fetch(mirror_at, value_at));
       DTP_HIP(hipStreamSynchronize(s));
       if ((st = check_stats()) != DTP_OK) return st;
       while (sweep < opt.max_sweeps) {
@@ -569,9 +585,18 @@ dtp_status dtp_coordinate_ascent(int32_t N, int32_t G, int32_t I, int32_t L, con
           // thread the next layer that none has taken.
           std::atomic<int> next{0};
           auto work = [&]() {
+            std::vector<int64_t> own;
             for (int i = next++; i < N; i = next++) {
               if (flags[i] == 0) continue;
               const int64_t* Mi = M + (size_t)i * I * L;
+              if (host_gains) {
+                const int64_t* Qu = (const int64_t*)mirror(0) + (size_t)i * G * I;
+                const bool dn = has_down && i + 1 < N;
+                neuron_gain(G, I, L, Qu, hs + (size_t)i * G,
+                            dn ? (const int64_t*)mirror(0) + nup + (size_t)i * I * G : nullptr,
+                            dn ? hs + (size_t)(i + 1) * G : nullptr, minimise, &own);
+                Mi = own.data();
+              }
               int32_t* nu_i = nus + (size_t)i * I;
               if (opt.dual_ascent_neurons)
                 balanced_assign_dual_ascent(I, L, Mi, kDualAscentIterations, kDualAscentDecay, nu_i, nullptr);
@@ -584,21 +609,19 @@ dtp_status dtp_coordinate_ascent(int32_t N, int32_t G, int32_t I, int32_t L, con
         // Head block, then (the heads on the device already moved) the next sweep's gains: always
         // after the first sweep, which another follows, and later where the copy costs no more
         // than the round trip that it saves.
-        const bool more = sweep < opt.max_sweeps && (sweep == 1 || m_bytes <= kEagerGainBytes);
-        DTP_HIP(hipMemcpyAsync(dev + nu_at, nus, nu_bytes, hipMemcpyHostToDevice, s));
+        const bool more = !host_gains && sweep < opt.max_sweeps && (sweep == 1 || m_bytes <= kEagerGainBytes);
+        DTP_HIP(host_gains && sweep == 1 ? send(h_at, end_at) : send(nu_at, best_at));
         if ((st = head_block()) != DTP_OK) return st;
         if (more && (st = gains()) != DTP_OK) return st;
-        const size_t from = more ? m_at : value_at;
-        DTP_HIP(hipMemcpyAsync(host.base + from, dev + from, nu_at - from, hipMemcpyDeviceToHost, s));
-        DTP_HIP(hipMemcpyAsync(host.base + h_at, dev + h_at, h_bytes, hipMemcpyDeviceToHost, s));
+        DTP_HIP(fetch(more ? m_at : value_at, nu_at));
         DTP_HIP(hipStreamSynchronize(s));
         const int64_t Jc = total(value);
         const bool improved = sweep == 1 || (minimise ? Jc < J_prev : Jc > J_prev);
         J_prev = Jc;
         if (!improved) break;
-        if (!more && sweep < opt.max_sweeps) {
+        if (!host_gains && !more && sweep < opt.max_sweeps) {
           if ((st = gains()) != DTP_OK) return st;
-          DTP_HIP(hipMemcpyAsync(host.base + m_at, dev + m_at, m_bytes, hipMemcpyDeviceToHost, s));
+          DTP_HIP(fetch(m_at, value_at));
           DTP_HIP(hipStreamSynchronize(s));
         }
       }
