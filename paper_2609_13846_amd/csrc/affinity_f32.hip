@@ -110,7 +110,9 @@ fold_f32_kernel(float* __restrict__ wcat, const float* __restrict__ w_o, int N, 
 // neurons each with a gate and an up accumulator, so both damage terms of a (token,
 // neuron) pair sit in one lane.  Stages of 16 contraction columns go through registers into
 // a padded LDS double buffer, the next one fetched during the current one's products.
-// 1/r needs no pass of its own: the four threads that stage a token row sum its squares.
+// 1/r needs no pass of its own: the four threads that stage a token row sum its squares, in 64
+// bits, since a quarter of a row is a long chain (in 32 the error of A grew by 3 to 5% and that
+// of the down statistic by 4 to 8% from d = 2,048 on, against 64 threads per row).
 // Bound by the fp32 matrix rate (64 FLOP per clock and SIMD): a stage's operands are 3
 // 16-byte LDS reads per 8 instructions.  S = 32 reads each operand half as often from L2;
 // S = 16 gives four times the blocks and a quarter of the serial work per tile, for launches
@@ -161,7 +163,7 @@ affinity_f32_kernel(AffinityF32Args p) {
     const float* xp = p.x + t * p.d + scol;
     const float* ap = p.attn + t * HD + scol;
     f32x4v av, bv[kBPer];
-    float ss = 0.0f;
+    double ss = 0.0;
     auto fetch = [&](int q) __attribute__((always_inline)) {
       av = f32x4v{0.0f, 0.0f, 0.0f, 0.0f};
       if (valid) av = *reinterpret_cast<const f32x4v*>(q < nq1 ? xp + q * kFK : ap + (q - nq1) * kFK);
@@ -175,8 +177,7 @@ affinity_f32_kernel(AffinityF32Args p) {
       for (int j = 0; j < kBPer; ++j)
         *reinterpret_cast<f32x4v*>(Bs[buf] + (srow + 64 * j) * kFRow + scol) = bv[j];
       if (op) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) ss = fmaf(av[e], av[e], ss);
+        ss += (double)(fmaf(av[0], av[0], av[1] * av[1]) + fmaf(av[2], av[2], av[3] * av[3]));
       }
     };
     typename M::Acc acc[2] = {};
@@ -215,7 +216,7 @@ affinity_f32_kernel(AffinityF32Args p) {
     // The row's last columns are in: its four threads are neighbours.
     ss += __shfl_xor(ss, 1, 64);
     ss += __shfl_xor(ss, 2, 64);
-    if (stages_tokens && scol == 0) rv[srow] = valid ? 1.0f / sqrtf(ss / (float)p.d + p.eps) : 0.0f;
+    if (stages_tokens && scol == 0) rv[srow] = valid ? (float)(1.0 / sqrt(ss / (double)p.d + (double)p.eps)) : 0.0f;
     stage(q++, false, false);
     // Operating point: c1 = silu'(g) u / r, c2 = silu(g) / r (both 1/r for the ADD score).
     float ds = 0.0f;
