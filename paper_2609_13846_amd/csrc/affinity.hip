@@ -789,13 +789,19 @@ struct LaunchShape {
 // operating point in every range, so it is weighed only where the tiles alone do not give
 // each CU two.
 //
-// A stage of 192, 128 and 64 tokens takes about 24 : 19 : 15 (one tile of 64 tokens of a
-// Qwen3-0.6B-shaped layer: launches of 30, 25 and 20 us; 16,384 tokens: 550 us in tiles of 192
-// and 571 in tiles of 128), so the low tiles are for slices that fill few CUs or whose last
-// tile would be mostly padding.  1,000 tokens: 59, 49 and 64 us; with ADD 39, 35 and 43; 256
-// tokens of an 8B-class layer, bound by its weights' way from HBM: 170, 153 and 257.  In heads of
-// three, five and six stages the highest tile spills registers between its heads (1,500 and
-// 5,000 tokens, 12 heads of 80: 57 and 155 us, against 69 and 139 in tiles of 128).
+// A stage of 192, 128 and 64 tokens counts 24 : 19 : 15, about what it takes where a launch has one
+// tile per block (one tile of 64 tokens of a Qwen3-0.6B-shaped layer: launches of 30, 25 and 20
+// us).  With every CU busy for many tiles the low ones cost less than that, 128 tokens 1.05 to
+// 1.09 times as much as 192 per token and 64 1.4 to 1.6 (19 : 24 is 1.19, 15 : 24 1.88), but still more
+// than 192, so that the order is the same.  In heads of three, five and six stages the FO score
+// spills registers between heads at 192 tokens (three: 170-176, 128 tokens take 0.95 to 0.99 of
+// the time of 192 per launch), which the costs of 26 and 25 stand for; the ADD score, which spills fewer,
+// does not show it (three stages: 318 us in tiles of 192, 333 in tiles of 128).  A tie goes to 128.
+// Over 142 launches of 300 to 65,536 tokens in heads of 16 to 256, each timed in tiles of all three
+// heights, the height that this chooses is the fastest or within 1.3% of it (with 26 for the heads
+// of five and six stages and for ADD too, up to 6.8% slower).  1,000 tokens of the Qwen3-0.6B shape:
+// 59, 49 and 64 us; with ADD 39, 35 and 43; 256 tokens of an 8B-class layer, bound by its weights'
+// way from HBM: 170, 153 and 257.
 LaunchShape choose_launch(const AffinityArgs& p, bool add, int T, int64_t max_rows) {
   const int64_t cus = device_cus(), groups = p.I_pad / kBlockNeurons;
   const int n1 = add ? 0 : p.nq1 + 8;  // the operating point's epilogue: about 8 stages
@@ -815,8 +821,8 @@ LaunchShape choose_launch(const AffinityArgs& p, bool add, int T, int64_t max_ro
     if (groups * mtiles < 2 * cus)
       for (int hs = 2; hs <= p.G; ++hs) weigh(tile, stage_cost, mtiles, cap, hs);
   };
-  weigh_tile(192, p.nqh == 3 || p.nqh == 5 || p.nqh == 6 ? 26 : 24);
   weigh_tile(128, 19);
+  weigh_tile(192, add ? 24 : p.nqh == 3 ? 26 : p.nqh == 5 || p.nqh == 6 ? 25 : 24);
   weigh_tile(64, 15);
   return best;
 }
