@@ -118,13 +118,14 @@ prep_gate_up_fragments_kernel(const uint16_t* __restrict__ w_gate, const uint16_
   }
 }
 
-// F_h[e, m] = sum_j W_o[j][h dh + e] W'[m][j] into column dP + h dhP + e of weight row m.  256
+// F_h[e, m] = sum_j W_o[j][h dh + e] W'[m][j] into column dP + h dhP + e of weight row m.  32 AF
 // columns n = h dh + e x 256 weight rows per block; n is the A side, so that a lane's four
 // accumulator elements are four consecutive columns of one row, an 8-byte store.
+template <int AF>
 __global__ void __launch_bounds__(512, 2)
 fold_kernel(uint16_t* wcat, const uint16_t* __restrict__ woT, int N, int dh, int dP, int dhP, int ks,
             int n_a, int n_b) {
-  using P = FragPipe<8, 4>;
+  using P = FragPipe<AF, 4>;
   __shared__ __attribute__((aligned(16))) uint16_t s0[P::kSlot];
   __shared__ __attribute__((aligned(16))) uint16_t s1[P::kSlot];
   __shared__ __attribute__((aligned(16))) uint16_t s2[P::kSlot];
@@ -136,8 +137,8 @@ fold_kernel(uint16_t* wcat, const uint16_t* __restrict__ woT, int N, int dh, int
       wcat + (int64_t)tb * P::kBRows * ks * kStage, (uint32_t)P::kBFrags * ks * 1024u);
   p.contract(s0, s1, s2, s3, nq);
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    const int n = ta * P::kARows + 16 * (p.wm * 8 + i) + 4 * (p.lane >> 4);
+  for (int i = 0; i < AF; ++i) {
+    const int n = ta * P::kARows + 16 * (p.wm * AF + i) + 4 * (p.lane >> 4);
     if (n >= N) continue;  // a multiple of 16: whole fragments
     const int k = dP + n / dh * dhP + n % dh;
     const bool last = n % dh / 16 == dh / 16 - 1;  // the fragment that ends its head
@@ -773,6 +774,35 @@ void launch_prep_gate_up(const uint16_t* w_gate, const uint16_t* w_up, const uin
     prep_gate_up_fragments_kernel<4, false><<<grid, kPrepThreads, 0, s>>>(w_gate, w_up, gamma, I, d, dP / 32, n, ks, out);
 }
 
+// W_o^T in fragments and the fold, in tiles of 256, 128 or 64 columns.  A block runs dP / 32 stages
+// whatever its height, one block per CU at a time; a stage takes about 32 : 18 : 12, so the height
+// with the fewest rounds of blocks, weighed so, is taken.  Loading a layer of d = 256, I = 1,024, 8
+// heads of 64: 21.9 us in tiles of 64 columns and 24.5 in tiles of 256 (16 blocks); of d = 1,040, I =
+// 2,810, 12 heads of 80: 66.9, 61.8 (128 columns) and 72.1; of d = 2,048, I = 8,192, 32 heads of 64:
+// 193, 152 and 142.
+template <int AF>
+void launch_fold_tiles(const uint16_t* w_o, int N, int d, int dh, int dP, int dhP, int I_pad, int ks, uint16_t* woT,
+                       uint16_t* wcat, hipStream_t s) {
+  const int n_a = (N + 32 * AF - 1) / (32 * AF), n_b = I_pad / kBlockNeurons, nq = dP / kStage;
+  const dim3 grid((N + 255) / 256 * 4, (nq + 1) / 2);
+  if (((uintptr_t)w_o & 15u) == 0)
+    transpose_fragments_kernel<2 * AF, false, true><<<grid, 256, 0, s>>>(w_o, nullptr, d, N, nq, woT);
+  else
+    transpose_fragments_kernel<2 * AF, false, false><<<grid, 256, 0, s>>>(w_o, nullptr, d, N, nq, woT);
+  fold_kernel<AF><<<n_a * n_b, 512, 0, s>>>(wcat, woT, N, dh, dP, dhP, ks, n_a, n_b);
+}
+
+void launch_fold(const uint16_t* w_o, int N, int d, int dh, int dP, int dhP, int I_pad, int ks, uint16_t* woT,
+                 uint16_t* wcat, hipStream_t s) {
+  const int64_t cus = device_cus(), n_b = I_pad / kBlockNeurons;
+  auto cost = [&](int columns, int64_t stage_cost) {
+    return ((N + columns - 1) / columns * n_b + cus - 1) / cus * stage_cost;
+  };
+  const int64_t high = cost(256, 32), mid = cost(128, 18), low = cost(64, 12);
+  (high <= mid && high <= low ? launch_fold_tiles<8> : mid <= low ? launch_fold_tiles<4> : launch_fold_tiles<2>)(
+      w_o, N, d, dh, dP, dhP, I_pad, ks, woT, wcat, s);
+}
+
 struct LaunchShape {
   int tile = kTokenPad;  // token rows per tile: 192, 128 or 64
   int mtiles = 1, splits = 1, hsplits = 1;
@@ -1196,17 +1226,8 @@ dtp_status dtp_layer_set_weights(dtp_layer L, const void* w_o, const void* gamma
       launch_prep_gate_up((const uint16_t*)w_gate, (const uint16_t*)w_up, (const uint16_t*)gamma, I, dm,
                           L->dP, L->I_pad, L->Kt / kStage, (uint16_t*)L->w, s);
       DTP_HIP(hipGetLastError());
-      const int n_a = (HD + 255) / 256, n_b = L->I_pad / kBlockNeurons, nq1 = L->dP / kStage;
-      const dim3 tg(n_a * 4, (nq1 + 1) / 2);
-      if (aligned16(w_o))
-        transpose_fragments_kernel<16, false, true><<<tg, 256, 0, s>>>((const uint16_t*)w_o, nullptr, dm, HD, nq1,
-                                                                   (uint16_t*)L->woT);
-      else
-        transpose_fragments_kernel<16, false, false><<<tg, 256, 0, s>>>((const uint16_t*)w_o, nullptr, dm, HD, nq1,
-                                                                    (uint16_t*)L->woT);
-      DTP_HIP(hipGetLastError());
-      fold_kernel<<<n_a * n_b, 512, 0, s>>>((uint16_t*)L->w, (const uint16_t*)L->woT, HD, dh, L->dP, L->dhP,
-                                            L->Kt / kStage, n_a, n_b);
+      launch_fold((const uint16_t*)w_o, HD, dm, dh, L->dP, L->dhP, L->I_pad, L->Kt / kStage, (uint16_t*)L->woT,
+                  (uint16_t*)L->w, s);
       DTP_HIP(hipGetLastError());
       st = down_norms((const uint16_t*)w_down, L, s);
       if (st != DTP_OK) return st;
