@@ -44,17 +44,17 @@ def oracle(wl, w, x, a, neurons=None):
     ("qwen3-0.6b-layer", 130, dict(n_q_heads=2, n_kv_groups=1)),    # one group
     ("qwen3-0.6b-layer", 129, dict(n_q_heads=8, n_kv_groups=8, head_dim=48)),  # H = G, dh % 32 = 16
     ("qwen3-0.6b-layer", 100, dict(n_q_heads=32, n_kv_groups=32, head_dim=64)),  # G at its limit
-    # the largest G with six copy buffers in the LDS, and the smallest that falls back to three
+    # G off the powers of two, one query head each
     ("qwen3-0.6b-layer", 90, dict(n_q_heads=26, n_kv_groups=26, head_dim=64)),
     ("qwen3-0.6b-layer", 90, dict(n_q_heads=27, n_kv_groups=27, head_dim=64)),
     ("danube3-500m", 64, dict(d_model=272, n_neurons=192)),         # d % 32 = 16
-    # two 64-deep stages and two 32-deep stages: the weight ring wraps within a tile
+    # four stages of the operating point, and one head of two stages and of one
     ("qwen3-0.6b-layer", 70, dict(d_model=64, n_q_heads=1, n_kv_groups=1, head_dim=64, n_neurons=128)),
     ("danube3-500m", 40, dict(d_model=32, n_q_heads=1, n_kv_groups=1, head_dim=32, n_neurons=64)),
-    # an odd number of stages (three), so the last one ends an unfinished pair of stages
+    # the same over more tokens than one tile
     ("qwen3-0.6b-layer", 600, dict(d_model=128, n_q_heads=1, n_kv_groups=1, head_dim=64, n_neurons=128)),
     ("danube3-500m", 300, dict(d_model=64, n_q_heads=1, n_kv_groups=1, head_dim=32, n_neurons=64)),
-    # three-stage heads (nine copy buffers): six stages, fewer than the ring, and nine
+    # one and two heads of three stages, which end off the first of the four slots
     ("danube3-500m", 300, dict(d_model=96, n_q_heads=1, n_kv_groups=1, head_dim=96, n_neurons=64)),
     ("danube3-500m", 600, dict(d_model=96, n_q_heads=2, n_kv_groups=1, head_dim=96, n_neurons=128)),
 ])
@@ -104,8 +104,8 @@ def test_affinity_8b_class_sampled_neurons():
 
 @pytest.mark.parametrize("G", [26, 32])
 def test_affinity_many_tiles_per_block_sampled_neurons(G):
-    """8,192 tokens at G = 26 (six copy buffers) and G = 32 (three): 32 tiles of 256 tokens
-    over 16 token splits, so each block runs two tiles back to back."""
+    """8,192 tokens of 26 and 32 groups of two stages per head: 64 tiles of 128 tokens over
+    32 splits on 256 CUs, so each block runs two tiles back to back."""
     wl, w, x, a = case("qwen3-0.6b-layer", 8192, n_q_heads=G, n_kv_groups=G, head_dim=64)
     announce(f"affinity G={G} T=8192 sampled neurons")
     A = hp.gpu_affinity(wl, w, x, a)
@@ -114,7 +114,8 @@ def test_affinity_many_tiles_per_block_sampled_neurons(G):
 
 
 def test_affinity_danube_many_tiles_per_block_sampled_neurons():
-    """8,192 Danube-shaped tokens (nine copy buffers): 32 tiles over 12 token splits."""
+    """8,192 Danube-shaped tokens, heads of three stages: 64 tiles of 128 tokens over 8
+    splits on 256 CUs, eight tiles per block."""
     wl, w, x, a = case("danube3-500m", 8192)
     announce("affinity danube3-500m T=8192 sampled neurons")
     A = hp.gpu_affinity(wl, w, x, a)
@@ -209,7 +210,7 @@ def add_oracle(wl, w, x, a, neurons=None):
     ("tiny", 512, {}),
     ("qwen3-0.6b-layer", 300, {}),
     ("danube3-500m", 257, {}),
-    ("danube3-500m", 64, dict(d_model=272, n_neurons=192)),         # 16-deep stages
+    ("danube3-500m", 64, dict(d_model=272, n_neurons=192)),         # d % 32 = 16
     ("qwen3-0.6b-layer", 100, dict(n_q_heads=32, n_kv_groups=32, head_dim=64)),
 ])
 def test_add_score_matches_oracle(name, T, shape):

@@ -4,9 +4,9 @@ counts that end a round of slots early, widths padded to whole stages, launches 
 KV groups, several tiles per block and several slices per call.
 
 Bars: A is held to the 1e-2 of bf16 inputs on entries above 1e-3 of the maximum.  The
-token statistic s_down squares g and u, whose W' rounding (2^-9 relative per term) a
-cancelling pre-activation magnifies by its condition number; over the hundreds of tokens
-here it averages below 2e-2 normwise, the bar for it.
+token statistic s_down squares g and u, whose W' rounding a cancelling pre-activation
+magnifies by its condition number: it is held entry by entry to the rounding model of
+tests/error_model.py, as everywhere, and to 1e-2 where that leaves room for it.
 """
 import numpy as np
 import pytest
@@ -14,6 +14,7 @@ import pytest
 from oracle import affinity as orc
 from oracle import down as orc_down
 from paper_2609_13846_amd import dtp, synth
+from tests import error_model as em
 from tests import helpers as hp
 
 pytestmark = pytest.mark.gpu
@@ -42,6 +43,10 @@ pytestmark = pytest.mark.gpu
     for T, I in ((1000, 4096), (18400, 1024))
     for dh, score in ((32, "fo"), (64, "down"), (96, "add"), (96, "down"), (128, "fo"), (160, "down"), (192, "add"),
                       (256, "down"))
+] + [  # nine heads of one, three and five stages, which close two rounds of four slots and begin a third
+    (T, score, dict(d_model=256, n_neurons=I, n_q_heads=9, n_kv_groups=3, head_dim=dh))
+    for T, I in ((1000, 4096), (18400, 1024))
+    for dh, score in ((32, "down"), (96, "fo"), (160, "down"), (160, "add"))
 ])
 def test_affinity_dispatch_edges(T, score, shape):
     import torch
@@ -70,5 +75,9 @@ def test_affinity_dispatch_edges(T, score, shape):
         hp.assert_affinity_close(A.cpu().numpy(), ref)
         s_ref = orc_down.down_token_stat(x=kw["x"], gamma=kw["gamma"], w_gate=kw["w_gate"], w_up=kw["w_up"],
                                          eps=wl.rms_eps, x_next=synth.to_f64(x_pre), eps_next=wl.rms_eps)
-        err = np.linalg.norm(s.cpu().numpy() - s_ref) / np.linalg.norm(s_ref)
-        assert err < 2e-2, err
+        s_m, s_sig, s_sec = em.down_stat_error(kw["x"], kw["gamma"], kw["w_gate"], kw["w_up"], wl.rms_eps,
+                                               synth.to_f64(x_pre), wl.rms_eps)
+        np.testing.assert_allclose(s_m, s_ref, rtol=1e-10)
+        rep = em.check_entrywise(s.cpu().numpy()[None, :], s_ref[None, :], s_sig[None, :], s_sec[None, :],
+                                 label="s_down")
+        print(f"[gpu] s_down {rep}", flush=True)
