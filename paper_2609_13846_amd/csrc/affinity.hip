@@ -823,24 +823,31 @@ struct LaunchShape {
 // tile per block (one tile of 64 tokens of a Qwen3-0.6B-shaped layer: launches of 30, 25 and 20
 // us).  With every CU busy for many tiles the low ones cost less than that, 128 tokens 1.05 to
 // 1.09 times as much as 192 per token and 64 1.4 to 1.6 (19 : 24 is 1.19, 15 : 24 1.88), but still more
-// than 192, so that the order is the same.  In heads of three, five and six stages the FO score
-// spills registers between heads at 192 tokens (three: 170-176, 128 tokens take 0.95 to 0.99 of
-// the time of 192 per launch), which the costs of 26 and 25 stand for; the ADD score, which spills fewer,
-// does not show it (three stages: 318 us in tiles of 192, 333 in tiles of 128).  A tie goes to 128.
-// Over 142 launches of 300 to 65,536 tokens in heads of 16 to 256, each timed in tiles of all three
-// heights, the height that this chooses is the fastest or within 1.3% of it (with 26 for the heads
-// of five and six stages and for ADD too, up to 6.8% slower).  1,000 tokens of the Qwen3-0.6B shape:
-// 59, 49 and 64 us; with ADD 39, 35 and 43; 256 tokens of an 8B-class layer, bound by its weights'
-// way from HBM: 170, 153 and 257.
+// than 192, so that the order is the same.
+//
+// In heads of three, five and six stages a tile of 192 tokens spills registers (FO 129 to 232, ADD
+// 18 to 102), in part per tile: most where the block's heads do not end a round of slots, whose
+// last heads then leave by a branch.  One head of 192, d = 128, I = 4,096, 30,000 tokens: 490 us in tiles
+// of 192 and 203 of 128; two heads of 96 369 and 218, four 354 and 297; 16 of 96 in d = 1,024 537 and
+// 524 (16,384 tokens), of 192 742 and 786, and with ADD 318 and 330, 558 and 594.
+//
+// The costs were fitted to 397 launches of 64 to 65,536 tokens, d = 16 to 4,096, 1 to 65 heads of 16 to
+// 256, each timed in tiles of all three heights: the height chosen is within 5% of the fastest in
+// all of them and within 2% in 386.  (One cost per number of stages, without the part per tile,
+// was up to 2.4 times slower.)  A tie goes to 128.
 LaunchShape choose_launch(const AffinityArgs& p, bool add, int T, int64_t max_rows) {
   const int64_t cus = device_cus(), groups = p.I_pad / kBlockNeurons;
   const int n1 = add ? 0 : p.nq1 + 8;  // the operating point's epilogue: about 8 stages
+  const bool spills = p.nqh == 3 || p.nqh == 5 || p.nqh == 6;
+  const int per_round = p.nqh == 6 ? 2 : 4;  // heads of a round of slots, where it matters
   LaunchShape best;
   auto weigh = [&](int tile, int stage_cost, int mtiles, int s, int hs) {
     const int64_t rounds = (groups * s * hs + cus - 1) / cus;
     const int64_t tiles = rounds * (mtiles / s) + (groups * hs * (mtiles % s) + cus - 1) / cus;
-    const int heads = (p.G + hs - 1) / hs * p.hpg;
-    const int64_t stages = n1 + (heads * p.nqh + 3) / 4 * 4;
+    const int most = (p.G + hs - 1) / hs * p.hpg, least = p.G / hs * p.hpg;  // heads of a block
+    int64_t stages = n1 + (most * p.nqh + 3) / 4 * 4;
+    if (spills && tile == 192)
+      stages += most % per_round || least % per_round ? (add ? 10 : 16) : p.nqh == 3 && !add ? 8 : 0;
     const int64_t cost = (tiles * stages + rounds * 12) * stage_cost;
     if (best.cost < 0 || cost < best.cost) best = {tile, mtiles, s, hs, cost};
   };
@@ -852,7 +859,7 @@ LaunchShape choose_launch(const AffinityArgs& p, bool add, int T, int64_t max_ro
       for (int hs = 2; hs <= p.G; ++hs) weigh(tile, stage_cost, mtiles, cap, hs);
   };
   weigh_tile(128, 19);
-  weigh_tile(192, add ? 24 : p.nqh == 3 ? 26 : p.nqh == 5 || p.nqh == 6 ? 25 : 24);
+  weigh_tile(192, spills && !add ? 25 : 24);
   weigh_tile(64, 15);
   return best;
 }

@@ -47,6 +47,9 @@ pytestmark = pytest.mark.gpu
     (T, score, dict(d_model=256, n_neurons=I, n_q_heads=9, n_kv_groups=3, head_dim=dh))
     for T, I in ((1000, 4096), (18400, 1024))
     for dh, score in ((32, "down"), (96, "fo"), (160, "down"), (160, "add"))
+] + [  # whole rounds of heads of three, five and six stages, in tiles of 192 tokens
+    (18400, score, dict(d_model=256, n_neurons=1024, n_q_heads=12, n_kv_groups=3, head_dim=dh))
+    for dh, score in ((96, "down"), (96, "add"), (160, "fo"), (192, "down"), (192, "add"))
 ])
 def test_affinity_dispatch_edges(T, score, shape):
     import torch
