@@ -386,12 +386,15 @@ __device__ __forceinline__ float damage(uint32_t w, float g, float u) {
 // rows of half 1 during half 0 of the next head's first.  The products of a head's first
 // stage start from zero.
 //
-// Bound by the matrix cores and the clock that they leave under this load (8B-class shape: MFMAs
-// busy 61% at 1.75 GHz; Qwen3-0.6B shape: 51% at 2.09 GHz; the same product, so time saved on
-// waits alone goes into the clock).  Launches of 32,768 Qwen-shaped and 16,384 8B-class and
-// Danube3-500M-shaped tokens: 1,120, 6,840 and 780 us, against 1,210, 7,180 and 860 us for 256
-// tokens x 64 neurons per block with the token fragments loaded straight into registers,
-// whose head epilogues ran with no products of their own wavefront beside them.
+// Bound by the matrix cores and by the waits between their stages: on the three layer shapes
+// measured the MFMAs are busy 50 to 62% of the SIMD cycles, at the 1.7 to 2.1 GHz that the clock holds
+// under this load, and a quarter to a third of the wave cycles stand at a wait.  (How much of the
+// clock power takes was not separated; MFMAs alone on random operands reach 80 to 82% of the
+// nominal rate.)  Launches of 32,768 Qwen3-0.6B-shaped and 16,384 8B-class and Danube3-500M-shaped
+// tokens: 1,040 to 1,140, 6,680 to 6,840 and 780 to 880 us, as the clock holds, against 1,210, 7,180 and
+// 860 us in the better runs of 256 tokens x 64 neurons per block with the token fragments loaded
+// straight into registers, whose head epilogues ran with no products of their own wavefront
+// beside them.
 template <int AF, bool ADD, bool DOWN, int NQH>
 struct AffinityBlock {
   using Pipe = FragPipe<AF, 4>;

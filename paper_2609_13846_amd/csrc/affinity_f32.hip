@@ -117,7 +117,7 @@ fold_f32_kernel(float* __restrict__ wcat, const float* __restrict__ w_o, int N, 
 // 16-byte LDS reads per 8 instructions.  S = 32 reads each operand half as often from L2;
 // S = 16 gives four times the blocks and a quarter of the serial work per tile, for launches
 // that would leave CUs without a block.  Measured against one thread per (neuron, token
-// lane), whose lanes each walked a weight row of their own: 15,318 -> 139 us at d = 512,
+// lane), whose lanes each walked a weight row of their own: 15,318 -> 140 us at d = 512,
 // I = 1536, 8 heads of 64, 2,048 tokens (93 TFLOP/s, matrix cores busy 62% at 2.25 GHz; a large
 // fp32 product reaches 154), and with S = 16 52 -> 12 us at d = 64, I = 128, 8 heads of 16, 512
 // tokens.  Of that, 180 -> 154 us are three wavefronts per SIMD, so that the 768 blocks run at

@@ -90,9 +90,10 @@ __device__ __forceinline__ float rows32_sum_sq(f32x4 lo, f32x4 hi) {
 // a block takes 32 AF rows (one chunk or two) of one group x 256 neurons.  The products'
 // order along the contraction and the order of the sums are those of
 // down_weight_bf16_kernel, so both give the same bits.  Bound by the matrix cores and the clock
-// that they leave: 721 GFLOP of the 8B-class shape in 521 us (1,385 TFLOP/s, as much as a
+// that they leave: 721 GFLOP of the 8B-class shape in 522 us at best (1,380 TFLOP/s, as much as a
 // large library product, at 1.90 GHz with the MFMAs busy 69% of the time and 1,344 blocks in
-// 5.25 rounds of 256 CUs), against 960 us for 128 x 128 tiles staged through registers.
+// 5.25 rounds of 256 CUs) and 533 to 608 over a row of calls, against 960 us for 128 x 128 tiles
+// staged through registers.
 template <int AF>
 __global__ void __launch_bounds__(512, 2)
 down_weight_frag_kernel(const uint16_t* __restrict__ qkv, const uint16_t* __restrict__ tw, int ks,

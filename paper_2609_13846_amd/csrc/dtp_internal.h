@@ -140,7 +140,8 @@ struct ScoreWorkspace {
   bool frozen = false;
   // The gain matrices of the neuron step, M[i][k][l] = sum_{g: h_i(g)=l} Q_up[i][g][k] +
   // sum_{g: h_{i+1}(g)=l} Q_down[i][k][g], negated with `minimise`; M dev [N][I][L], from this
-  // workspace's h.  Set by score_workspace_create.
+  // workspace's h.  Set by score_workspace_create (a pointer, so that the host sources link
+  // without the kernels, as the host-only checks build them).
   dtp_status (*neuron_gains)(const ScoreWorkspace& ws, const int64_t* Q_up, const int64_t* Q_down,
                              int minimise, int64_t* M, hipStream_t stream) = nullptr;
   // The neuron step itself for two devices (L = 2), from this workspace's h: the canonical

@@ -259,8 +259,8 @@ namespace {
 // The transpose of a row-major [n_j][n_k] bf16 matrix in fragment-major layout (rows k < 64
 // gridDim.x, columns j < 32 ks): element (k, j) = in[j][k], times gamma[j] and rounded to bf16
 // with SCALE, zero for k >= n_k or j >= n_j.  64 x 64 tiles through LDS, 16-byte reads along k
-// with VEC (n_k and the address allow them) and writes of whole fragments.  HBM-bound: 40 us
-// for 4,096 x 14,336 (106 us with 2-byte accesses).
+// with VEC (n_k and the address allow them) and writes of whole fragments.  HBM-bound: 40 to 49 us
+// for 4,096 x 14,336, scaled (106 us with 2-byte accesses).
 template <int F, bool SCALE, bool VEC>
 __global__ void __launch_bounds__(256)
 transpose_fragments_kernel(const uint16_t* __restrict__ in, const uint16_t* __restrict__ gamma, int n_j,

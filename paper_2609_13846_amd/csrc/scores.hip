@@ -185,7 +185,7 @@ neuron_gain_kernel(const int64_t* __restrict__ Q_up, const int64_t* __restrict__
 // block per layer: the keys d + 2^50 (|d| is below 2^50: two matrices' codes sum to 2^48 each)
 // in LDS or, for more than kTwoLds of them, in scratch; a radix selection of seven bytes;
 // then the ties in index order.  Bound by its chain of barriers: 17 us at G = 8, I = 3072.
-// With it the ascent of such a layer takes 138 us instead of 197, most of the difference being
+// With it the ascent of such a layer takes 135 us instead of 197, most of the difference being
 // the copies and the round trip to the host between two sweeps.
 constexpr int kTwoThreads = 1024;
 constexpr int kTwoLds = 7168;  // keys held in LDS (56 KB)
