@@ -134,8 +134,9 @@ dtp_status dtp_affinity_accumulate_down(dtp_layer layer, const void* x, const vo
  * bf16: MFMA over d with gamma' * w^d_k rounded to bf16, fp32 sums of squares; requires
  * d and I multiples of 8.  f32: plain FMAs (small shapes).  Scratch of G*I*ceil((H/G+2)*dh
  * /128) floats, and for bf16 copies of the scaled, transposed W_down and of the projections
- * (about (I + (H + 2 G) dh) * d bf16, rounded up to whole tiles), is taken from the
- * stream-ordered allocator and returned before exit. */
+ * (about (I + (H + 2 G) dh) * d bf16, rounded up to whole tiles, each group's rows to 128), is
+ * taken from the stream-ordered allocator and returned before exit.  (Where the copies would
+ * take launches of 2^32 threads the matrices are read in place.) */
 dtp_status dtp_down_weights(int32_t d_model, int32_t n_neurons, int32_t n_q_heads,
                             int32_t n_kv_groups, int32_t head_dim, dtp_dtype dtype,
                             const void* w_q, const void* w_k, const void* w_v,
